@@ -353,8 +353,9 @@ int dckv_dense_decode(int32_t num_q_heads, int32_t num_kv_heads, int32_t head_di
  *   G          device [cols, cols] fp32, written in full (both triangles)
  *   workspace  device, at least dckv_gram_workspace_bytes (may be NULL
  *              when that is 0), 256-byte aligned
- * Products and sums are fp32 (MFMA f32) in a fixed order: bitwise
- * reproducible.  Errors: DCKV_EINVAL (shape, null pointer), DCKV_EDTYPE,
+ * Sums are fp32 in a fixed order: bitwise reproducible.  Products are those
+ * of bf16 samples, exact in fp32, or of fp32 values (fp32 or centred samples)
+ * taken as three bf16 parts each, to below 2^-22 of a product.  Errors: DCKV_EINVAL (shape, null pointer), DCKV_EDTYPE,
  * DCKV_EALIGN, DCKV_EWORKSPACE, DCKV_EHIP; nothing is launched on error. */
 int dckv_gram_workspace_bytes(int64_t rows, int32_t cols, int32_t center, size_t* bytes);
 int dckv_gram(const void* A, int32_t dtype, int64_t rows, int32_t cols, int32_t center, float* G,

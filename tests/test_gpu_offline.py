@@ -54,6 +54,47 @@ def test_gram_matches_oracle(rows, cols, dtype, center):
     assert np.array_equal(got, got.T)                       # mirrored tiles are exact copies
 
 
+# edges of the 64-, 128- and 192-column tiles and of the 32- and 64-row stages,
+# one row to several stages of the three-buffer ring, and more row blocks than
+# a tile adds up by itself (64 of 256 rows); both ways of taking the samples
+# (bf16 as they are; fp32 or centred in three bf16 parts).  The bound is the
+# one above: every product of bf16 samples is exact in fp32, and the three
+# products of parts that are left out are below 2^-22 of a term, the bound's
+# 2 (rows + 8) 2^-24 at one row.
+EDGES = [(1, 8), (31, 56), (32, 64), (33, 72), (63, 128), (64, 136), (65, 192), (127, 200),
+         (191, 384), (193, 392), (257, 1152), (16641, 24)]
+
+
+@pytest.mark.parametrize("rows, cols", EDGES)
+@pytest.mark.parametrize("dtype, center", [("bf16", False), ("bf16", True), ("f32", False), ("f32", True)])
+def test_gram_at_tile_edges(rows, cols, dtype, center):
+    from paper_2607_24331_amd import gram
+    g = np.random.default_rng(rows + cols)
+    A = (g.standard_normal((rows, cols)) * 3 + g.standard_normal(cols)[None, :]).astype(np.float32)
+    At = torch.from_numpy(A).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    A64 = At.double().cpu().numpy()
+    got = gram(At, center=center).double().cpu().numpy()
+    ref = ocal.gram(oc.centered(A64) if center else A64)
+    assert np.all(np.abs(got - ref) <= _gram_bound(A64, center, rows))
+    assert np.array_equal(got, got.T)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_gram_of_infinities_and_nans(dtype):
+    # one infinity in column 3, one NaN in column 70: those rows and columns of
+    # G are what sums of products give (infinite with the partner's sign, NaN
+    # against a zero), every other element is unchanged
+    from paper_2607_24331_amd import gram
+    g = np.random.default_rng(3)
+    A = g.integers(-4, 5, (40, 136)).astype(np.float32)        # exact: sums of small integers
+    A[7, 3], A[9, 70] = -np.inf, np.nan
+    got = gram(torch.from_numpy(A).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16),
+               center=False).cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = np.stack([(A[:, i:i + 1] * A).sum(axis=0) for i in range(A.shape[1])])
+    assert np.array_equal(got, ref, equal_nan=True)
+
+
 def test_gram_is_bitwise_reproducible():
     from paper_2607_24331_amd import gram
     A = torch.randn(777, 200, device="cuda")
