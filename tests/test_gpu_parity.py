@@ -352,6 +352,42 @@ def test_append_random_within_one_ulp():
         assert np.all(Zg[5] == 0)        # skipped slot untouched
 
 
+# each kernel of the append at the edges of its tiles: 1 to 32 tokens (one and
+# two 16-token tiles), then enough tokens over 2933 columns for 64 x 64, 128 x
+# 64, 128 x 128 and 128 x 256 tiles, none of the counts a multiple of a tile;
+# five 64-wide stages (not a multiple of the stage buffers).  Same bound as above.
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32, 33, 65, 257, 400, 769, 1409])
+def test_append_at_tile_edges(n):
+    from paper_2607_24331_amd import Plan, latent_append
+    from workloads.inputs import to_storage
+    ranks = (301, 280, 320, 255, 290, 317, 270, 289, 297)
+    m, rv, rk = 320, 313, sum(ranks)
+    plan = Plan(m, 36, 36, 80, [g for g in range(9) for _ in range(4)], ranks, rv)
+    g = np.random.default_rng(n)
+    x = to_storage(g.standard_normal((n, m)), "bf16")
+    Lk = to_storage(g.standard_normal((m, rk)) / np.sqrt(m), "bf16")
+    Lv = to_storage(g.standard_normal((m, rv)) / np.sqrt(m), "bf16")
+    pages = n // 64 + 2
+    slots = g.permutation(pages * 64)[:n].astype(np.int64)
+    place = slots.copy()
+    if n > 2:
+        slots[1], slots[n - 1] = -1, pages * 64             # skipped tokens
+    pool = plan.new_pool(pages)
+    latent_append(plan, dev(x, "bf16"), dev(Lk.T, "bf16"), dev(Lv.T, "bf16"),
+                  torch.from_numpy(slots).cuda(), pool)
+    table = np.arange(pages, dtype=np.int32)[None, :]
+    Zk, Zv = olayout.unpack(pool.float().cpu().numpy(), table, 0, pages * 64, rk, rv)
+    live = (slots >= 0) & (slots < pages * 64)
+    for Zg, L in ((Zk, Lk), (Zv, Lv)):
+        exact = oappend.down_project(x, L)
+        rounded = obf16.round_to_bf16(exact)
+        bound = obf16.ulp_bf16(rounded) + m * 2.0 ** -24 * oappend.abs_bound(x, L)
+        assert np.all(np.abs(Zg[place] - rounded)[live] <= bound[live])
+        untouched = np.ones(pages * 64, bool)
+        untouched[place[live]] = False
+        assert np.all(Zg[untouched] == 0)
+
+
 # ------------------------------------------------------------ full workloads
 @pytest.mark.parametrize("name", [n for n in WORKLOAD_NAMES if n != "tiny_mha_f32"])
 def test_full_workload_sampled_rows(name):
