@@ -474,6 +474,90 @@ hipError_t launch_append_few(const dckv_plan& p, const void* x, int32_t n_tok, c
   return hipGetLastError();
 }
 
+// fp32 latents on the fp32 matrix instruction (m a multiple of 16): fp32
+// products and sums.  A 32-token x 32-column tile a work-group, its four waves
+// splitting k (a small layer has few tiles: 256 tokens x 256 columns make 64,
+// each a chain of m / 64 load steps a wave); a wave takes 16-byte pieces of 16
+// k of 32 + 32 rows, four steps of them in flight, element e of a piece
+// feeding the e-th of four 16x16x4 products (any order of k serves both
+// operands).  The waves' sums are added in wave order through LDS.  256 tokens
+// x 512 x 256: 8 us against 70 us on append_valu.
+__global__ __launch_bounds__(256) void append_f32(const float* __restrict__ x,
+                                                  const float* __restrict__ Lk,
+                                                  const float* __restrict__ Lv,
+                                                  const int64_t* __restrict__ slot,
+                                                  float* __restrict__ pool, int n_tok, int m, int RK,
+                                                  int RKp, int rv, int64_t page_elems,
+                                                  int64_t value_base, int64_t num_pages) {
+  constexpr int U = 4;                                 // load steps in flight
+  __shared__ floatx4_t red[4][4][64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int ncols = RKp + rv, col0 = 32 * blockIdx.y, tok0 = 32 * blockIdx.x;
+  const int nst = m >> 4, s0 = w * nst / 4, s1 = (w + 1) * nst / 4;
+  const float* src[4];                                 // two token tiles, two column tiles
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    src[i] = x + int64_t(min(tok0 + 16 * i + lr, n_tok - 1)) * m + 4 * lq;
+    const int c = col0 + 16 * i + lr;
+    src[2 + i] = (c < RK ? Lk + int64_t(c) * m
+                  : c < RKp ? Lk                       // padding column: written as zero below
+                            : Lv + int64_t(min(c - RKp, rv - 1)) * m) + 4 * lq;
+  }
+  floatx4_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  floatx4_t v[U][4];
+  auto load = [&](int k, int st) {                     // clamped: in bounds
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[k][i] = *reinterpret_cast<const floatx4_t*>(src[i] + 16 * min(st, nst - 1));
+  };
+#pragma unroll
+  for (int k = 0; k < U; ++k) load(k, s0 + k);
+  for (int st = s0; st < s1; st += U) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      if (st + k < s1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[k][i][e], v[k][2 + j][e], acc[i][j], 0, 0, 0);
+      }
+      load(k, st + k + U);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) red[w][2 * i + j][lane] = acc[i][j];
+  __syncthreads();
+  // wave w finishes tile (w / 2, w % 2): tokens 4 lq + v, column lr
+  floatx4_t t = red[0][w][lane];
+#pragma unroll
+  for (int k = 1; k < 4; ++k) t += red[k][w][lane];
+  const int c = col0 + 16 * (w & 1) + lr;
+  if (c >= ncols) return;
+  const int64_t slot_end = num_pages * DCKV_PAGE_TOKENS;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int tok = tok0 + 16 * (w >> 1) + 4 * lq + q;
+    if (tok >= n_tok) continue;
+    const int64_t sl = slot[tok];
+    if (sl < 0 || sl >= slot_end) continue;
+    float* pg = pool + (sl / DCKV_PAGE_TOKENS) * page_elems;
+    const int sp = int(sl % DCKV_PAGE_TOKENS);
+    if (c < RKp)
+      pg[key_elem(sp, c)] = c < RK ? t[q] : 0.f;
+    else
+      pg[value_base + value_elem(sp, c - RKp)] = t[q];
+  }
+}
+
 template <typename T>
 hipError_t launch_append_t(const dckv_plan& p, const void* x, int32_t n_tok, const void* Lk,
                            const void* Lv, const int64_t* slot, void* pool, int64_t num_pages,
@@ -492,6 +576,14 @@ hipError_t launch_append_t(const dckv_plan& p, const void* x, int32_t n_tok, con
 hipError_t launch_append(const dckv_plan& p, const void* x, int32_t n_tok, const void* L_keys,
                          const void* L_value, const int64_t* slot, void* pool, int64_t num_pages,
                          hipStream_t stream) {
+  if (p.dtype == DCKV_F32 && p.m % 16 == 0) {
+    const int ncols = p.RKp + p.rv;
+    hipLaunchKernelGGL(append_f32, dim3((n_tok + 31) / 32, (ncols + 31) / 32), dim3(256), 0, stream,
+                       static_cast<const float*>(x), static_cast<const float*>(L_keys),
+                       static_cast<const float*>(L_value), slot, static_cast<float*>(pool), n_tok,
+                       p.m, p.RK, p.RKp, p.rv, p.page_elems, p.value_base, num_pages);
+    return hipGetLastError();
+  }
   if (p.dtype == DCKV_F32)
     return launch_append_t<float>(p, x, n_tok, L_keys, L_value, slot, pool, num_pages, stream);
   if (p.m % kBK == 0) {

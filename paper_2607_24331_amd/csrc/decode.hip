@@ -47,11 +47,35 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(const float* __restrict_
 }
 
 // ------------------------------------------------- split (portable VALU)
+// Eight (or, for fp32, twice four) consecutive latents as floats.
+template <typename T>
+__device__ __forceinline__ void load8(const T* p, float (&v)[8]) {
+  if constexpr (sizeof(T) == 4) {
+    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+    const uint4 a = *reinterpret_cast<const uint4*>(p);
+    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[2 * j] = __uint_as_float(w[j] << 16);
+      v[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
+    }
+  }
+}
+
 // One 256-thread block per (split, query head, query row): query row
 // bq = b * Q + i is query i of sequence b, which sees the first
 // T_b - Q + i + 1 cache positions (causal inside the chunk of Q).  Scores:
-// 4 threads per token, each summing a quarter of the group's rank.  Values:
-// each thread owns value columns tid, tid+256, ...
+// four threads (one of each wave) a token, each taking eight columns of every
+// 32-column key chunk that meets the group's columns (columns outside it are
+// left out, whatever they hold).  Softmax: every wave reduces the page's
+// scores by itself.  Values: each thread owns value columns tid, tid + 256,
+// ..., and where r_v <= 128 one token half of column tid % 128, the halves
+// added at the end.  Latency-bound on the small layers it serves: 8 heads x 64
+// over 256 tokens take 6 us in four splits (36 us as one split of scalar
+// loads).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void split_valu(
     const float* __restrict__ qt, const T* __restrict__ pool, int64_t num_pages,
@@ -61,9 +85,10 @@ __global__ __launch_bounds__(kThreads) void split_valu(
   const int split = blockIdx.x, h = blockIdx.y, bq = blockIdx.z;
   const int b = bq / tb.n_queries, qi = bq % tb.n_queries;
   const int tid = threadIdx.x;
-  __shared__ float qs[DCKV_MAX_GROUP_RANK];
+  __shared__ float qs[DCKV_MAX_GROUP_RANK + 64];       // folded query from its first chunk's column on
   __shared__ float part[4][DCKV_PAGE_TOKENS];
   __shared__ float ps[DCKV_PAGE_TOKENS];
+  __shared__ float half_acc[128];
 
   int T_b = seq_lens[b];
   T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
@@ -72,7 +97,10 @@ __global__ __launch_bounds__(kThreads) void split_valu(
   const int t1 = min(t0 + split_tokens, T_q);
   const int r = tb.rank_of_q[h];
   const int koff = tb.koff_of_q[h];
-  for (int j = tid; j < r; j += kThreads) qs[j] = qt[int64_t(bq) * tb.qlen + tb.qoff[h] + j];
+  const int lead = koff & 31, c_lo = koff >> 5;          // columns before the group's in its first chunk
+  const int nch = ((koff + r - 1) >> 5) - c_lo + 1;
+  for (int j = tid; j < 32 * nch; j += kThreads)
+    qs[j] = j >= lead && j < lead + r ? qt[int64_t(bq) * tb.qlen + tb.qoff[h] + j - lead] : 0.f;
   __syncthreads();
 
   float acc[kAccPerThread];
@@ -80,6 +108,7 @@ __global__ __launch_bounds__(kThreads) void split_valu(
   for (int i = 0; i < kAccPerThread; ++i) acc[i] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   const int slot = tid & (DCKV_PAGE_TOKENS - 1), quarter = tid >> 6;
+  const bool halves = rv <= 128;
 
   for (int tok = t0; tok < t1; tok += DCKV_PAGE_TOKENS) {
     const int n = min(DCKV_PAGE_TOKENS, t1 - tok);
@@ -89,50 +118,87 @@ __global__ __launch_bounds__(kThreads) void split_valu(
     float sp = 0.f;
     if (valid && slot < n) {
       // chunk-major keys: column c of this slot at (c/32)*2048 + slot*32 + c%32
-      const T* kslot = pg + slot * 32;
-      for (int k = quarter; k < r; k += 4) {
-        const int c = koff + k;
-        sp = fmaf(qs[k], to_f32(kslot[(c >> 5) * 2048 + (c & 31)]), sp);
+      const T* kslot = pg + int64_t(c_lo) * 2048 + slot * 32 + 8 * quarter;
+#pragma unroll 4
+      for (int c = 0; c < nch; ++c) {
+        float v[8];
+        load8(kslot + c * 2048, v);
+        const int j0 = 32 * c + 8 * quarter;
+        const bool inside = j0 >= lead && j0 + 8 <= lead + r;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool in = inside || (j0 + j >= lead && j0 + j < lead + r);
+          sp = fmaf(qs[j0 + j], in ? v[j] : 0.f, sp);
+        }
       }
     }
     part[quarter][slot] = sp;
     __syncthreads();
-    if (tid < DCKV_PAGE_TOKENS)
-      ps[tid] = (valid && tid < n) ? (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])
-                                   : -INFINITY;
-    __syncthreads();
-    float cmax = -INFINITY;
-    for (int t = 0; t < n; ++t) cmax = fmaxf(cmax, ps[t]);
-    const float m_new = fmaxf(m_run, cmax);
-    __syncthreads();
-    if (m_new == -INFINITY) continue;  // uniform: no valid token so far
-    const float alpha = exp2f(m_run - m_new);
-    if (tid < DCKV_PAGE_TOKENS) ps[tid] = tid < n ? exp2f(ps[tid] - m_new) : 0.f;
-    __syncthreads();
-    float csum = 0.f;
-    for (int t = 0; t < n; ++t) csum += ps[t];
-    l_run = l_run * alpha + csum;
+    // every wave: the page's scores, one a lane, and their maximum
+    const float s = (valid && slot < n) ? (part[0][slot] + part[1][slot]) + (part[2][slot] + part[3][slot])
+                                        : -INFINITY;
+    float cmax = s;
 #pragma unroll
-    for (int i = 0; i < kAccPerThread; ++i) {
-      const int j = tid + i * kThreads;
-      if (j < rv) {
-        float a = acc[i] * alpha;
-        if (valid) {
-          // tile-major values: column j of slot t at (j/16)*1024 + (t/32)*512 + (j%16)*32 + t%32
-          const T* vcol = pg + value_base + int64_t(j >> 4) * 1024 + (j & 15) * 32;
-          for (int t = 0; t < n; ++t) a = fmaf(ps[t], to_f32(vcol[(t >> 5) * 512 + (t & 31)]), a);
+    for (int o = 32; o >= 1; o >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, o));
+    const float m_new = fmaxf(m_run, cmax);
+    if (m_new == -INFINITY) {          // uniform: no valid token so far
+      __syncthreads();                 // part is rewritten next page
+      continue;
+    }
+    const float alpha = exp2f(m_run - m_new);
+    const float p = s == -INFINITY ? 0.f : exp2f(s - m_new);
+    float csum = p;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) csum += __shfl_xor(csum, o);
+    if (quarter == 0) ps[slot] = p;
+    __syncthreads();
+    l_run = l_run * alpha + csum;
+    // tile-major values: column j of slot t at (j/16)*1024 + (t/32)*512 + (j%16)*32 + t%32
+    auto column = [&](int j, int h0, int h1, float a) {
+      const T* vcol = pg + value_base + int64_t(j >> 4) * 1024 + (j & 15) * 32;
+      for (int hf = h0; hf < h1; ++hf) {
+        if (n >= 32 * hf + 32) {
+          float v[4][8];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) load8(vcol + hf * 512 + 8 * k, v[k]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a = fmaf(ps[32 * hf + 8 * k + e], v[k][e], a);
+        } else {
+          for (int t = 32 * hf; t < n; ++t) a = fmaf(ps[t], to_f32(vcol[hf * 512 + (t & 31)]), a);
         }
-        acc[i] = a;
+      }
+      return a;
+    };
+    if (halves) {
+      const int j = tid & 127, hf = tid >> 7;
+      acc[0] *= alpha;
+      if (valid && j < rv) acc[0] = column(j, hf, hf + 1, acc[0]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kAccPerThread; ++i) {
+        const int j = tid + i * kThreads;
+        if (j < rv) {
+          acc[i] *= alpha;
+          if (valid) acc[i] = column(j, 0, 2, acc[i]);
+        }
       }
     }
     m_run = m_new;
-    __syncthreads();
+    __syncthreads();                   // part and ps are rewritten next page
   }
 
   const int64_t row = (int64_t(bq) * tb.n_q_heads + h) * n_split + split;
   if (tid == 0) {
     part_ml[row * 2 + 0] = m_run;
     part_ml[row * 2 + 1] = l_run;
+  }
+  if (halves) {
+    if (tid >= 128) half_acc[tid - 128] = acc[0];
+    __syncthreads();
+    if (tid < rv) part_acc[row * rv + tid] = acc[0] + half_acc[tid];
+    return;
   }
 #pragma unroll
   for (int i = 0; i < kAccPerThread; ++i) {
@@ -142,6 +208,8 @@ __global__ __launch_bounds__(kThreads) void split_valu(
 }
 
 // ------------------------------------------------------ merge + up-project
+// The up-projection's ranks are dealt to 256 / ceil64(d_h) thread groups whose
+// sums are added in group order.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void merge_upproject(
     const float* __restrict__ part_ml, const float* __restrict__ part_acc,
@@ -152,6 +220,7 @@ __global__ __launch_bounds__(kThreads) void merge_upproject(
   const int n = tb.n_kv_heads * dh;
   const int kv = h / tb.q_per_kv;
   __shared__ float ash[DCKV_MAX_VALUE_RANK];
+  __shared__ float red[kThreads];
   const int64_t row0 = (int64_t(b) * tb.n_q_heads + h) * n_split;
   float M = -INFINITY;
   for (int s = 0; s < n_split; ++s) M = fmaxf(M, part_ml[(row0 + s) * 2]);
@@ -172,11 +241,19 @@ __global__ __launch_bounds__(kThreads) void merge_upproject(
     ash[j] = a * inv;
   }
   __syncthreads();
-  for (int d = tid; d < dh; d += kThreads) {
-    float acc = 0.f;
+  const int width = (dh + 63) & ~63, groups = kThreads / width;      // d_h <= 256: at least one
+  const int d = tid % width, g = tid / width;
+  float acc = 0.f;
+  if (d < dh && g < groups) {
     const T* col = Rv + int64_t(kv) * dh + d;
-    for (int j = 0; j < rv; ++j) acc = fmaf(ash[j], to_f32(col[int64_t(j) * n]), acc);
-    o[d] = acc;
+#pragma unroll 8
+    for (int j = g; j < rv; j += groups) acc = fmaf(ash[j], to_f32(col[int64_t(j) * n]), acc);
+  }
+  red[tid] = acc;
+  __syncthreads();
+  if (tid < dh) {
+    for (int k = 1; k < groups; ++k) acc += red[k * width + tid];
+    o[tid] = acc;
   }
 }
 
@@ -313,7 +390,11 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context)
       L = std::max<int64_t>(DCKV_PAGE_TOKENS, (L + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS * DCKV_PAGE_TOKENS);
       L = std::min<int64_t>(L, mfma_max_split_tokens());
     } else {
-      L = kValuSplitTokens;
+      // kValuSplitTokens, less while that leaves compute units without a block
+      const int64_t work = int64_t(batch) * p.Q * p.Hq * max_context;
+      L = (work + kTargetWorkgroups - 1) / kTargetWorkgroups;
+      L = std::max<int64_t>(DCKV_PAGE_TOKENS, (L + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS * DCKV_PAGE_TOKENS);
+      L = std::min<int64_t>(L, kValuSplitTokens);
     }
   }
   if (s.mfma && L > mfma_max_split_tokens()) s.mfma = false;   // an explicit split beyond the cap

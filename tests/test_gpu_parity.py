@@ -388,6 +388,48 @@ def test_append_at_tile_edges(n):
         assert np.all(Zg[untouched] == 0)
 
 
+# fp32 latents: the matrix kernel at the edges of its 32 x 32 tiles and with
+# fewer 16-wide k steps than waves (m = 48), and the portable kernel where m is
+# not a multiple of 16 (m = 200); the fp32 dot-product bound of any order
+@pytest.mark.parametrize("n, m", [(1, 48), (31, 272), (33, 512), (70, 96), (70, 200)])
+def test_append_f32_at_tile_edges(n, m):
+    from paper_2607_24331_amd import Plan, latent_append
+    ranks, rv = (37, 41), 45
+    rk = sum(ranks)
+    plan = Plan(m, 4, 4, 64, (0, 1, 1, 0), ranks, rv, "f32")
+    g = np.random.default_rng(n + m)
+    x = g.standard_normal((n, m)).astype(np.float32)
+    Lk = g.standard_normal((m, rk)).astype(np.float32)
+    Lv = g.standard_normal((m, rv)).astype(np.float32)
+    slots = g.permutation(128)[:n].astype(np.int64)
+    pool = plan.new_pool(2)
+    latent_append(plan, dev(x, "f32"), dev(Lk.T, "f32"), dev(Lv.T, "f32"),
+                  torch.from_numpy(slots).cuda(), pool)
+    table = np.arange(2, dtype=np.int32)[None, :]
+    Zk, Zv = olayout.unpack(pool.cpu().numpy(), table, 0, 128, rk, rv)
+    for Zg, L in ((Zk, Lk), (Zv, Lv)):
+        exact = oappend.down_project(x, L)
+        bound = m * 2.0 ** -24 * oappend.abs_bound(x, L) + np.abs(exact) * 2.0 ** -23
+        assert np.all(np.abs(Zg[slots] - exact) <= bound)
+
+
+# the portable decode over fp32 latents: groups that start inside a key chunk,
+# value ranks up to 128 (token halves) and above, head sizes 64, 96 and 128,
+# partial pages, several splits chosen by the call
+@pytest.mark.parametrize("name", ["mha_odd", "gqa_uneven", "single_group", "head96"])
+def test_f32_decode_all_rows(name):
+    wl, inp, _ = _small_inputs(name, "f32")
+    plan = plan_for(wl)
+    out = run_decode(inp, plan, gpu_pool_with_append(inp, plan))
+    errs = []
+    for (b, h), o in _all_rows(inp).items():
+        if wl.seq_lens[b] == 0:
+            assert np.all(out[b, h] == 0)
+            continue
+        errs.append(row_rel_err(out[b, h], o))
+    assert max(errs) <= TOL_REL_ROW_F32
+
+
 # ------------------------------------------------------------ full workloads
 @pytest.mark.parametrize("name", [n for n in WORKLOAD_NAMES if n != "tiny_mha_f32"])
 def test_full_workload_sampled_rows(name):
