@@ -189,8 +189,10 @@ int dckv_decode_workspace_bytes(const dckv_plan* plan, int32_t batch, int32_t ma
 typedef struct dckv_launch_info {
   int32_t kernels;       /* 0 portable VALU kernels, 1 single-pass MFMA split kernel,
                             2 two-pass MFMA kernels */
-  int32_t split_tokens;  /* context tokens a split (a value chunk on the two-pass path) */
-  int32_t n_split;       /* splits (chunks) of the longest sequence */
+  int32_t split_tokens;  /* context tokens a split (a value chunk on the two-pass path);
+                            where the library cuts several sequences of the single-pass
+                            kernel by their actual lengths: the fixed cut it starts from */
+  int32_t n_split;       /* splits (chunks) of the longest sequence, likewise */
   int32_t head_slices;   /* row slices of the MFMA kernels (each slice's score work
                             reads its groups' key chunks; on the single-pass kernel
                             each also reads the value part), 1 on the portable path */
@@ -239,8 +241,8 @@ int dckv_latent_append(const dckv_plan* plan, const void* x, int32_t n_tok,
  *               max_context) bytes, 256-byte aligned; its contents on entry
  *               do not matter and are overwritten
  * Results are bitwise reproducible for a fixed plan and inputs: the work
- * split depends only on split_tokens and every reduction runs in a fixed
- * order.  batch == 0 is a no-op; batch * Q is at most 65535. */
+ * split depends only on split_tokens or, where the library chooses it, on the
+ * sequence lengths, and every reduction runs in a fixed order.  batch == 0 is a no-op; batch * Q is at most 65535. */
 int dckv_decode(const dckv_plan* plan, const float* q, int32_t batch, const void* pool,
                 int64_t num_pages, const int32_t* page_table, int32_t max_pages,
                 const int32_t* seq_lens, int32_t max_context, const void* R_keys,

@@ -414,6 +414,29 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context)
     s.off_acc = s.off_ml + align_up(rows * 2 * nh * sizeof(float), 256);
     s.off_opart = s.off_acc + align_up(rows * nh * size_t(p.rv) * sizeof(float), 256);
     s.bytes = s.off_opart + align_up(size_t(batch) * p.Q * p.Hq * p.rv * sizeof(float), 256);
+    // Balanced splits: several sequences, no split size asked for, and a head
+    // size whose fold kernel cuts them.  Never more splits than the fixed cut
+    // has (their partials share its workspace), and a whole number of rounds
+    // over the compute units where that leaves one a sequence and none longer
+    // than the split kernel's page list.  Fixed splits are sized by
+    // max_context: 64 sequences of 1024 to 8192 tokens leave a third of the
+    // compute units without work (split kernel 370 us, balanced 292; the
+    // record's load before all others costs equal lengths 0.7 us of 88); one
+    // sequence is cut evenly as it is.
+    if (p.split_tokens == 0 && batch >= 2 && batch <= kSchedMaxBatch && units <= kSchedMaxUnits &&
+        (p.dh == 64 || p.dh == 128)) {
+      const int64_t npm = (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS;
+      const int64_t cap = mfma_max_split_tokens() / DCKV_PAGE_TOKENS;
+      const int64_t target = std::max<int64_t>(1, kTargetWorkgroups / p.mfma.n_slices);
+      int64_t U = units;
+      const int64_t whole = U / target * target;
+      if (whole >= batch && int64_t(batch) * ((npm + cap - 1) / cap) <= whole) U = whole;
+      s.n_sched = int32_t(U);
+      s.n_units = int32_t((U + 7) / 8 * 8);
+      s.off_sched = s.bytes;
+      s.sched_bytes = align_up(size_t(U) * sizeof(SchedUnit) + size_t(batch) * sizeof(SchedSeq), 256);
+      s.bytes += s.sched_bytes;
+    }
   } else {
     const size_t rows = size_t(batch) * p.Q * p.Hq * s.n_split;
     s.off_acc = s.off_ml + align_up(rows * 2 * sizeof(float), 256);

@@ -150,6 +150,97 @@ __global__ __launch_bounds__(64) void fold_blocks(const float* __restrict__ q,
   }
 }
 
+// cut_sequences: the balanced splits, by one wave (up to four sequences a
+// lane).  The split length is the smallest number of pages L for which the
+// sequences make at most n_units splits of at most L pages; a sequence's
+// splits are cut evenly, numbered sequence after sequence.  It runs beside the
+// fold's work-groups and must end with them (5 us), so every step is one
+// round trip: 64 lengths are tried at once, one a lane, from the least
+// possible on, and the units find their sequences by a scan over the first
+// units' marks.
+__device__ __forceinline__ int ceil_div(int n, int d, float inv) {   // n < 2^24
+  int q = int(float(n) * inv);
+  q -= q * d > n ? 1 : 0;
+  q += n - q * d >= d ? 1 : 0;
+  return q + (q * d < n ? 1 : 0);
+}
+__device__ __forceinline__ int wave_scan(int v, int lane, bool mx) {   // inclusive, sums or maxima
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int w = __shfl_up(v, o);
+    if (lane >= o) v = mx ? max(v, w) : v + w;
+  }
+  return v;
+}
+__device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
+  constexpr int N = kSchedMaxBatch / 64, M = kSchedMaxUnits / 64;
+  __shared__ int np_lds[kSchedMaxBatch], first[kSchedMaxBatch], owner[kSchedMaxUnits];
+  const int lane = threadIdx.x;
+  int np[N], pages = 0;                      // pages < 2^25 a sequence, < 2^17 units of 2^8 in all
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int b = lane * N + k;
+    const int t = sa.seq_lens[min(b, batch - 1)];
+    np[k] = b < batch ? (max(0, min(t, sa.max_context)) + 63) >> 6 : 0;
+    np_lds[b] = np[k];
+    pages += np[k];
+  }
+#pragma unroll
+  for (int k = 0; k < M; ++k) owner[lane + 64 * k] = 0;
+  pages = __shfl(wave_scan(pages, lane, false), 63);
+  int L = max(1, (pages + sa.n_units - 1) / sa.n_units);
+  __syncthreads();
+  for (;; L += 64) {                         // ends: kPageSlots pages make few enough splits
+    const int d = L + lane;
+    const float inv = 1.f / float(d);
+    int n = 0;
+    for (int b = 0; b < batch; ++b) n += ceil_div(np_lds[b], d, inv);
+    const unsigned long long fits = __ballot(n <= sa.n_units);
+    if (fits) {
+      L += __ffsll(fits) - 1;
+      break;
+    }
+  }
+  const float inv = 1.f / float(L);
+  int s[N], sum = 0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    s[k] = ceil_div(np[k], L, inv);
+    sum += s[k];
+  }
+  int before = wave_scan(sum, lane, false);
+  const int total = __shfl(before, 63);      // <= n_units
+  before -= sum;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int b = lane * N + k;
+    first[b] = before;
+    if (s[k] > 0) owner[before] = b;
+    if (b < batch) sa.seqs[b] = SchedSeq{before, s[k]};
+    before += s[k];
+  }
+  __syncthreads();
+  int own[M];                                // this lane's units M lane .. + M - 1
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    own[k] = owner[lane * M + k];
+    if (k) own[k] = max(own[k], own[k - 1]);
+  }
+  const int last = wave_scan(own[M - 1], lane, true), prev = __shfl_up(last, 1);
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    const int u = lane * M + k;
+    if (u >= sa.n_units) break;
+    SchedUnit e = {0, 0, 0, 0};
+    if (u < total) {
+      const int b = lane ? max(own[k], prev) : own[k], i = u - first[b];
+      const int n = ceil_div(np_lds[b], L, inv), q = np_lds[b] / n, r = np_lds[b] - q * n;
+      e = SchedUnit{b, i * q + min(i, r), q + (i < r ? 1 : 0), 0};
+    }
+    sa.units[u] = e;
+  }
+}
+
 // fold_mfma: the same blocks as fold_blocks, as one small product a (slice,
 // slot, 32-column chunk): the batch's query rows of the slot's head (B x d_h)
 // times the R rows of the chunk's columns (d_h x 32), on MFMA.  One wave;
@@ -162,13 +253,18 @@ template <int KS>
 __global__ __launch_bounds__(64) void fold_mfma(const float* __restrict__ q,
                                                 const bf16* __restrict__ Rk,
                                                 u32x4* __restrict__ qblk_ws, int batch, float scale,
-                                                HeadTables tb, MfmaTables mt) {
+                                                HeadTables tb, MfmaTables mt, SchedArgs sa) {
+  int id = blockIdx.x;
+  if (sa.units && --id < 0) {                 // one work-group more, the first, cuts the balanced splits
+    cut_sequences(sa, batch);
+    return;
+  }
   const int J = mt.n_slices;
   // 1-D grid, XCD-aware: the 16 slots of one (slice, chunk) write
   // interleaved 16-byte pieces of the same blocks, so they share an XCD
   // (work-group ids equal mod 8) and its L2 merges the pieces
   const int ngrp = J * mt.max_pairs;
-  const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+  const int xcd = id & 7, pos = id >> 3;
   const int grp = 8 * (pos >> 4) + xcd, j = pos & 15;
   if (grp >= ngrp) return;
   const int slice = grp / mt.max_pairs, pr = grp % mt.max_pairs;
@@ -272,13 +368,13 @@ __global__ __launch_bounds__(64) void fold_mfma(const float* __restrict__ q,
 // relative to the split maximum, with m and l already in part_ml), so there
 // is no key phase and no online softmax: the whole split's weights are
 // staged in LDS once, and the pages stream values only (KR == VR).
-template <int W, int NT, int MTW, int KR, bool PW = false>
+template <int W, int NT, int MTW, int KR, bool PW = false, bool SCHED = false>
 __global__ __launch_bounds__(W * 64, 1) void split_mfma(
     const u32x4* __restrict__ qblk_ws, const bf16* __restrict__ pool, int64_t num_pages,
     const int32_t* __restrict__ page_table, int max_pages, const int32_t* __restrict__ seq_lens,
     int max_context, int split_tokens, int n_split, int n_units, int RK, int rv,
     int64_t page_elems, int64_t value_base, float* __restrict__ part_ml, float* __restrict__ part,
-    MfmaTables mt, const bf16* __restrict__ pw) {
+    MfmaTables mt, const bf16* __restrict__ pw, const SchedUnit* __restrict__ sched) {
   constexpr int NH = 16 * NT;                          // head slots of the slice
   constexpr int SW = (4 * NT < W) ? 4 * NT : W;        // waves holding score tiles
   constexpr int MPW = (4 * NT) / SW;                   // score M-tiles (16 tokens) a scoring wave
@@ -295,12 +391,19 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   const int grp = Lid / (8 * J), rr = Lid % (8 * J);
   const int slice = rr / 8;
   const int u = grp * 8 + (rr % 8);       // all slices of unit u share an XCD (ids equal mod 8)
-  if (u >= n_units) return;               // n_units = batch * n_split (the grid is padded)
-  const int b = u / n_split, split = u % n_split;
+  if (u >= n_units) return;               // n_units = batch * n_split, or the balanced splits (the grid is padded)
+  // fixed splits: sequence and first page by number; balanced ones (SCHED) by
+  // the unit's record
+  SchedUnit un = {0, 0, 0, 0};
+  if constexpr (SCHED) {
+    un = sched[u];
+    if (un.pages == 0) return;            // fewer splits than units
+  }
+  const int b = SCHED ? un.b : u / n_split, split = SCHED ? 0 : u % n_split;
+  const int page0 = SCHED ? un.page0 : split * (split_tokens >> 6);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, provably uniform
   const int lr = lane & 15, lq = lane >> 4;
-  const int t0 = split * split_tokens;
 
   // ---- LDS carve-up
   const int nch0 = mt.kln[slice][0][0] + mt.kln[slice][0][1];
@@ -325,19 +428,20 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   constexpr int SWc = (4 * NT < W) ? 4 * NT : W;
   const int hrow_raw = mt.hord[slice][min(16 * ((min(w, SWc - 1) * ((4 * NT) / SWc)) / 4) + lr, kSliceHeads - 1)];
   const int hrow = w < SWc ? hrow_raw : -1;
-  const int pg_lane = page_table[int64_t(b) * max_pages + min((t0 >> 6) + tid, max_pages - 1)];
-  const u32x4* qsrc = qblk_ws + int64_t(b * J + slice) * mt.max_pairs * 128;
   const int n16 = npairs * 128;
+  const int pg_lane = page_table[int64_t(b) * max_pages + min(page0 + tid, max_pages - 1)];
+  const u32x4* qsrc = qblk_ws + int64_t(b * J + slice) * mt.max_pairs * 128;
   u32x4 qv[kQblkLoads];
   if constexpr (!PW) {
 #pragma unroll
     for (int k = 0; k < kQblkLoads; ++k) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
   }
-  int pid0 = (t0 >> 6) < max_pages ? page_table[int64_t(b) * max_pages + (t0 >> 6)] : -1;
-  pid0 = __builtin_amdgcn_readfirstlane((pid0 >= 0 && pid0 < num_pages) ? pid0 : -1);
+  int pid0 = page0 < max_pages ? page_table[int64_t(b) * max_pages + page0] : -1;
   int T_b = seq_lens[b];
+  const int t0 = 64 * page0;
+  pid0 = __builtin_amdgcn_readfirstlane((pid0 >= 0 && pid0 < num_pages) ? pid0 : -1);
   T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
-  const int t1 = min(t0 + split_tokens, T_b);
+  const int t1 = min(SCHED ? t0 + 64 * un.pages : t0 + split_tokens, T_b);
   if (t0 >= t1) return;                   // the merge only reads splits holding tokens
   const int np = (t1 - t0 + 63) / 64;
 
@@ -681,7 +785,7 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   }
 
   // ---- partials: (m[NH], l[NH]) compact per split, acc[rank][NH] (head slot fastest)
-  const int64_t prow = (int64_t(b) * J + slice) * n_split + split;
+  const int64_t prow = SCHED ? int64_t(slice) * n_units + u : (int64_t(b) * J + slice) * n_split + split;
   if (w == 0 && lane < 16) {
     float* pml = part_ml + prow * (2 * NH);
 #pragma unroll
@@ -723,13 +827,14 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
 // flight for long merges, four for short ones.
 // Fixed order: group g sums splits g, g + G, ... ascending, then the G group
 // sums are added in order.
-template <int NH, bool LONG, int MR>
+template <int NH, bool LONG, int MR, bool SCHED>
 __global__ __launch_bounds__(256) void merge_mfma(const float* __restrict__ part_ml,
                                                   const float* __restrict__ part,
                                                   const int32_t* __restrict__ seq_lens,
                                                   int max_context, int split_tokens, int n_split,
                                                   int rv, float* __restrict__ amerged,
-                                                  HeadTables tb, MfmaTables mt) {
+                                                  HeadTables tb, MfmaTables mt,
+                                                  const SchedSeq* __restrict__ seqs) {
   constexpr int TPR = MR * NH / 4;            // threads a split row
   constexpr int G = 256 / TPR;                // split groups
   constexpr int SUB = 256 / NH;               // split groups of pass 1
@@ -741,11 +846,20 @@ __global__ __launch_bounds__(256) void merge_mfma(const float* __restrict__ part
   __shared__ float red[256];
   __shared__ float sM[NH], sInvL[NH];
   __shared__ float4 racc[256];
-  int T_b = seq_lens[b];
-  T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
-  const int ns = (T_b + split_tokens - 1) / split_tokens;
-  const float* ml = part_ml + (int64_t(b) * J + slice) * n_split * (2 * NH);
-  const float* pb = part + (int64_t(b) * J + slice) * n_split * int64_t(NH) * rv;
+  // the sequence's splits: rows of the partials from row0 on
+  int ns;
+  int64_t row0 = (int64_t(b) * J + slice) * n_split;
+  if constexpr (SCHED) {                      // n_split: the units of all sequences
+    const SchedSeq sq = seqs[b];
+    ns = sq.units;
+    row0 = int64_t(slice) * n_split + sq.u0;
+  } else {
+    int T_b = seq_lens[b];
+    T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
+    ns = (T_b + split_tokens - 1) / split_tokens;
+  }
+  const float* ml = part_ml + row0 * (2 * NH);
+  const float* pb = part + row0 * int64_t(NH) * rv;
 
   // pass 1
   {
@@ -887,7 +1001,8 @@ template <int W, int NT, int MTW, int KR>
 hipError_t launch_split(const dckv_plan& p, const DecodeShape& sh, const u32x4* qblk,
                         const void* pool, int64_t num_pages, const int32_t* page_table,
                         int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
-                        size_t lds, hipStream_t stream, const bf16* pw = nullptr) {
+                        size_t lds, hipStream_t stream, const bf16* pw = nullptr,
+                        const SchedUnit* sched = nullptr) {
   if (pw) {                               // the rotary decode's value pass
     if constexpr (KR == (((2 * MTW) % 16 == 0) ? 16 : 12)) {
       auto kern = split_mfma<W, NT, MTW, KR, true>;
@@ -896,29 +1011,32 @@ hipError_t launch_split(const dckv_plan& p, const DecodeShape& sh, const u32x4* 
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(sh.n_units * p.mfma.n_slices), dim3(W * 64), lds, stream, qblk,
                          static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
-                         sh.max_context, sh.split_tokens, sh.n_split, sh.batch * sh.n_split, p.RK,
-                         p.rv, p.page_elems, p.value_base, part_ml, part, p.mfma, pw);
+                         sh.max_context, sh.split_tokens, sh.n_split, sh.batch * sh.n_split,
+                         p.RK, p.rv, p.page_elems, p.value_base, part_ml, part, p.mfma, pw,
+                         static_cast<const SchedUnit*>(nullptr));
       return hipGetLastError();
     }
     return hipErrorInvalidValue;
   }
-  auto kern = split_mfma<W, NT, MTW, KR>;
+  auto kern = sched ? split_mfma<W, NT, MTW, KR, false, true> : split_mfma<W, NT, MTW, KR>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
   const int grid = sh.n_units * p.mfma.n_slices;
+  const int n_units = sched ? sh.n_sched : sh.batch * sh.n_split;
   if (p.prof_before && p.prof_after)   // events stamped by the kernel's own dispatch
     hipExtLaunchKernelGGL(kern, dim3(grid), dim3(W * 64), uint32_t(lds), stream, p.prof_before,
                           p.prof_after, 0u, qblk, static_cast<const bf16*>(pool), num_pages,
                           page_table, max_pages, seq_lens, sh.max_context, sh.split_tokens,
-                          sh.n_split, sh.batch * sh.n_split, p.RK, p.rv, p.page_elems,
-                          p.value_base, part_ml, part, p.mfma, static_cast<const bf16*>(nullptr));
+                          sh.n_split, n_units, p.RK, p.rv, p.page_elems,
+                          p.value_base, part_ml, part, p.mfma, static_cast<const bf16*>(nullptr),
+                          sched);
   else
     hipLaunchKernelGGL(kern, dim3(grid), dim3(W * 64), lds, stream, qblk,
                        static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
-                       sh.max_context, sh.split_tokens, sh.n_split, sh.batch * sh.n_split, p.RK,
+                       sh.max_context, sh.split_tokens, sh.n_split, n_units, p.RK,
                        p.rv, p.page_elems, p.value_base, part_ml, part, p.mfma,
-                       static_cast<const bf16*>(nullptr));
+                       static_cast<const bf16*>(nullptr), sched);
   return hipGetLastError();
 }
 
@@ -926,28 +1044,28 @@ template <int W, int NT, int MTW>
 hipError_t launch_split_r(const dckv_plan& p, const DecodeShape& sh, const u32x4* qt,
                           const void* pool, int64_t num_pages, const int32_t* page_table,
                           int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
-                          size_t lds, hipStream_t stream) {
+                          size_t lds, hipStream_t stream, const SchedUnit* sched) {
   if constexpr (MTW <= 12) {               // the plan mixes block sizes only here
     if (p.mfma.ring == 12)
       return launch_split<W, NT, MTW, 12>(p, sh, qt, pool, num_pages, page_table, max_pages,
-                                          seq_lens, part_ml, part, lds, stream);
+                                          seq_lens, part_ml, part, lds, stream, nullptr, sched);
     if (p.mfma.ring == 14)
       return launch_split<W, NT, MTW, 14>(p, sh, qt, pool, num_pages, page_table, max_pages,
-                                          seq_lens, part_ml, part, lds, stream);
+                                          seq_lens, part_ml, part, lds, stream, nullptr, sched);
   }
   if (p.mfma.ring != 16) return hipErrorInvalidValue;
   return launch_split<W, NT, MTW, 16>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens,
-                                      part_ml, part, lds, stream);
+                                      part_ml, part, lds, stream, nullptr, sched);
 }
 
 template <int W, int NT>
 hipError_t launch_split_w(const dckv_plan& p, const DecodeShape& sh, const u32x4* qt,
                           const void* pool, int64_t num_pages, const int32_t* page_table,
                           int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
-                          size_t lds, hipStream_t stream) {
+                          size_t lds, hipStream_t stream, const SchedUnit* sched) {
 #define DCKV_SPLIT(M)                                                                   \
   return launch_split_r<W, NT, M>(p, sh, qt, pool, num_pages, page_table, max_pages, \
-                                  seq_lens, part_ml, part, lds, stream)
+                                  seq_lens, part_ml, part, lds, stream, sched)
   switch (p.mfma.mtw_t) {
     case 6: DCKV_SPLIT(6);
     case 8: DCKV_SPLIT(8);
@@ -985,18 +1103,20 @@ hipError_t launch_split_pw(const dckv_plan& p, const DecodeShape& sh, const void
 // position-free and the rotary decode.
 hipError_t launch_merge_upproj(const dckv_plan& p, const DecodeShape& sh, const int32_t* seq_lens,
                                const float* part_ml, const float* part, float* amerged,
-                               const void* R_value, float* out, hipStream_t stream) {
+                               const void* R_value, float* out, hipStream_t stream,
+                               const SchedSeq* seqs = nullptr) {
   // the deep-batch merge only for long split lists: its registers would cost
   // the short merges (many small work-groups) their occupancy
   const bool lng = sh.n_split >= 128;
-  auto kern = sh.merge_ranks == 16
-                  ? (p.mfma.nt == 1 ? (lng ? merge_mfma<16, true, 16> : merge_mfma<16, false, 16>)
-                                    : (lng ? merge_mfma<32, true, 16> : merge_mfma<32, false, 16>))
-                  : (p.mfma.nt == 1 ? (lng ? merge_mfma<16, true, 8> : merge_mfma<16, false, 8>)
-                                    : (lng ? merge_mfma<32, true, 8> : merge_mfma<32, false, 8>));
+#define DCKV_MERGE(NH, MR)                                                                      \
+  (seqs ? (lng ? merge_mfma<NH, true, MR, true> : merge_mfma<NH, false, MR, true>)              \
+        : (lng ? merge_mfma<NH, true, MR, false> : merge_mfma<NH, false, MR, false>))
+  auto kern = sh.merge_ranks == 16 ? (p.mfma.nt == 1 ? DCKV_MERGE(16, 16) : DCKV_MERGE(32, 16))
+                                   : (p.mfma.nt == 1 ? DCKV_MERGE(16, 8) : DCKV_MERGE(32, 8));
+#undef DCKV_MERGE
   hipLaunchKernelGGL(kern, dim3(sh.batch * p.mfma.n_slices, sh.n_rchunks), dim3(256), 0, stream,
-                     part_ml, part, seq_lens, sh.max_context, sh.split_tokens, sh.n_split, p.rv,
-                     amerged, p.tables, p.mfma);
+                     part_ml, part, seq_lens, sh.max_context, sh.split_tokens,
+                     seqs ? sh.n_sched : sh.n_split, p.rv, amerged, p.tables, p.mfma, seqs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_upproj(p, sh.batch * p.Q, amerged, R_value, out, stream);
@@ -1005,18 +1125,19 @@ hipError_t launch_merge_upproj(const dckv_plan& p, const DecodeShape& sh, const 
 }  // namespace
 
 hipError_t launch_fold(const dckv_plan& p, const MfmaTables& mt, int32_t batch, const float* q,
-                       const void* R_keys, void* qblk, hipStream_t stream) {
+                       const void* R_keys, void* qblk, const SchedArgs& sched, hipStream_t stream) {
   const float scale = kLog2e / std::sqrt(float(p.dh));
   // d_h 64 or 128: one wave a (slice, slot, chunk) for all sequences, on
   // MFMA; other head sizes: one wave a (sequence, slice, slot, chunk)
   if (p.dh == 64 || p.dh == 128) {
     auto kern = p.dh == 64 ? fold_mfma<2> : fold_mfma<4>;
     const int ngrp = mt.n_slices * mt.max_pairs;
-    hipLaunchKernelGGL(kern, dim3(8 * 16 * ((ngrp + 7) / 8)), dim3(64), 0, stream, q,
-                       static_cast<const bf16*>(R_keys), static_cast<u32x4*>(qblk), batch, scale,
-                       p.tables, mt);
+    hipLaunchKernelGGL(kern, dim3(8 * 16 * ((ngrp + 7) / 8) + (sched.units ? 1 : 0)), dim3(64), 0,
+                       stream, q, static_cast<const bf16*>(R_keys), static_cast<u32x4*>(qblk), batch,
+                       scale, p.tables, mt, sched);
     return hipGetLastError();
   }
+  if (sched.units) return hipErrorInvalidValue;   // decode_shape asks for them with d_h 64 or 128 only
   hipLaunchKernelGGL(fold_blocks, dim3(batch * mt.n_slices, 16, mt.max_pairs), dim3(64), 0, stream, q,
                      static_cast<const bf16*>(R_keys), static_cast<u32x4*>(qblk), scale, p.tables,
                      mt);
@@ -1044,18 +1165,26 @@ hipError_t launch_decode_mfma(const dckv_plan& p, const DecodeShape& sh, const f
   float* part = reinterpret_cast<float*>(ws + sh.off_acc);
   float* amerged = reinterpret_cast<float*>(ws + sh.off_opart);
   const size_t lds = mfma_split_lds_bytes(p);
-  hipError_t e = launch_fold(p, p.mfma, sh.batch, q, R_keys, qt, stream);
+  SchedArgs sa{};
+  if (sh.n_sched > 0) {
+    sa.seq_lens = seq_lens;
+    sa.max_context = sh.max_context;
+    sa.n_units = sh.n_sched;
+    sa.units = reinterpret_cast<SchedUnit*>(ws + sh.off_sched);
+    sa.seqs = reinterpret_cast<SchedSeq*>(sa.units + sh.n_sched);
+  }
+  hipError_t e = launch_fold(p, p.mfma, sh.batch, q, R_keys, qt, sa, stream);
   if (e != hipSuccess) return e;
   if (p.mfma.waves == 4)
     e = p.mfma.nt == 1
-            ? launch_split_w<4, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream)
-            : launch_split_w<4, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream);
+            ? launch_split_w<4, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
+            : launch_split_w<4, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
   else
     e = p.mfma.nt == 1
-            ? launch_split_w<8, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream)
-            : launch_split_w<8, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream);
+            ? launch_split_w<8, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
+            : launch_split_w<8, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
   if (e != hipSuccess) return e;
-  return launch_merge_upproj(p, sh, seq_lens, part_ml, part, amerged, R_value, out, stream);
+  return launch_merge_upproj(p, sh, seq_lens, part_ml, part, amerged, R_value, out, stream, sa.seqs);
 }
 
 size_t rope_value_lds_bytes(const dckv_plan& p, int32_t split_tokens) {

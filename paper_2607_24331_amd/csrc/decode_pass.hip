@@ -1485,7 +1485,7 @@ hipError_t launch_decode_pass(const dckv_plan& p, const DecodeShape& sh, const f
   float* vpart = reinterpret_cast<float*>(ws + sh.off_acc);
   float* vel = reinterpret_cast<float*>(ws + sh.off_ml);
   float* amerged = reinterpret_cast<float*>(ws + sh.off_opart);
-  hipError_t e = launch_fold(p, p.pass, sh.batch, q, R_keys, qt, stream);
+  hipError_t e = launch_fold(p, p.pass, sh.batch, q, R_keys, qt, SchedArgs{}, stream);
   if (e != hipSuccess) return e;
   e = p.pass.nt == 1 ? launch_score<1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens,
                                        pw, stream)

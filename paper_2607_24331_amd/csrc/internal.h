@@ -88,6 +88,11 @@ struct DecodeShape {
   int32_t n_units;          // batch * n_split rounded up to a multiple of 8: grid units (MFMA path)
   int32_t n_rchunks;        // value-rank chunks of the merge (MFMA path)
   int32_t merge_ranks = 8;  // value ranks a merge work-group (8 or 16)
+  // balanced splits (single-pass path, several sequences, automatic split size):
+  // the fold kernel cuts the sequences' actual pages into n_sched splits
+  int32_t n_sched;          // splits (grid units) in all, 0: fixed splits of split_tokens
+  size_t off_sched;         // workspace: n_sched unit records, then a record a sequence
+  size_t sched_bytes;       // its size
   // two-pass path
   int32_t npm;              // pages of the longest sequence: ceil(max_context / 64), at least 1
   int32_t unit_pages;       // pages a score work-group
@@ -106,6 +111,25 @@ struct DecodeShape {
   size_t off_p;             // softmax weights (bf16): rotary splits; two-pass pages (with
                             // their (e, l) records)
   size_t bytes;
+};
+
+// Balanced splits: unit u takes pages [page0, page0 + pages) of sequence b
+// (pages 0: nothing); sequence b's units are u0 .. u0 + units - 1.
+struct SchedUnit {
+  int32_t b, page0, pages, pad;
+};
+struct SchedSeq {
+  int32_t u0, units;
+};
+constexpr int kSchedMaxBatch = 256;   // four sequences a lane of the wave that cuts them
+constexpr int kSchedMaxUnits = 512;   // eight units a lane
+
+// What the fold kernel needs to cut them (units null: fixed splits).
+struct SchedArgs {
+  const int32_t* seq_lens;
+  int32_t max_context, n_units;
+  SchedUnit* units;
+  SchedSeq* seqs;
 };
 
 // Launch shape of one uncompressed decode call (dense.hip).
@@ -176,8 +200,9 @@ hipError_t launch_decode_pass(const dckv_plan& p, const DecodeShape& sh, const f
 hipError_t launch_upproj(const dckv_plan& p, int32_t batch_rows, const float* amerged,
                          const void* R_value, float* out, hipStream_t stream);
 // Folded-query MFMA operand blocks (decode_mfma.hip) for the tables `mt`.
+// With sched.units the same launch cuts the balanced splits (d_h 64 or 128).
 hipError_t launch_fold(const dckv_plan& p, const MfmaTables& mt, int32_t batch, const float* q,
-                       const void* R_keys, void* qblk, hipStream_t stream);
+                       const void* R_keys, void* qblk, const SchedArgs& sched, hipStream_t stream);
 
 // MFMA decode path (decode_mfma.hip).
 size_t mfma_split_lds_bytes(const dckv_plan& p);

@@ -15,7 +15,10 @@ namespace {
 // Each GPU the library runs on holds its own copy of this array until the
 // process ends.  Host code never uses the name as an address: it takes the
 // device address from hipGetSymbolAddress, once per device.
-static __device__ __align__(256) unsigned char scratch[DCKV_NOALLOC_SCRATCH_BYTES];
+// The records of balanced splits come on top of the size that calls are held to.
+constexpr size_t kSchedBytes = kSchedMaxUnits * sizeof(SchedUnit) + kSchedMaxBatch * sizeof(SchedSeq);
+static_assert(kSchedBytes % 256 == 0, "room for the records as decode_shape rounds them");
+static __device__ __align__(256) unsigned char scratch[DCKV_NOALLOC_SCRATCH_BYTES + kSchedBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -52,7 +55,7 @@ extern "C" int dckv_decode_noalloc(const dckv_plan* p, const float* q, int32_t b
   int st = dckv::check_decode("decode_noalloc", p, q, batch, pool, num_pages, page_table,
                               max_pages, seq_lens, max_context, R_keys, R_value, out, &shape);
   if (st != DCKV_OK || batch == 0) return st;
-  if (shape.bytes > size_t(DCKV_NOALLOC_SCRATCH_BYTES))
+  if (shape.bytes - shape.sched_bytes > size_t(DCKV_NOALLOC_SCRATCH_BYTES))
     return dckv::fail(DCKV_EWORKSPACE,
                       "decode_noalloc: this call needs %zu bytes of scratch; the fixed device "
                       "array holds %zu (use dckv_decode with a workspace)",

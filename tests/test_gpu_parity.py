@@ -352,6 +352,45 @@ def test_append_random_within_one_ulp():
         assert np.all(Zg[5] == 0)        # skipped slot untouched
 
 
+# balanced splits: a short and a long sequence, empty ones, equal lengths,
+# lengths beyond max_context, as many sequences as one wave cuts (256) and one
+# more (fixed splits), several queries (two row slices)
+SCHED = {
+    "short_and_long": ((1, 20001), 1), "ragged": (tuple((97 * i * i) % 1500 for i in range(40)), 1),
+    "equal": ((640,) * 8, 1), "empty": ((0, 0, 0), 1), "one_used": ((0, 5000, 0, 0), 1),
+    "beyond": ((300, 900, 5000), 1), "b256": (tuple((i * 37) % 200 for i in range(256)), 1),
+    "b257": (tuple((i * 37) % 200 for i in range(257)), 1),
+    "queries": ((2000, 130, 64, 777), 8),
+}
+
+
+@pytest.mark.parametrize("name", list(SCHED))
+def test_balanced_splits(name):
+    from paper_2607_24331_amd import Plan, decode
+    lens, Q = SCHED[name]
+    B, top = len(lens), 1000 if name == "beyond" else max(max(lens), 64)
+    layer = (512, 8, 4, 64, (0, 1, 1, 0), (60, 45), 144)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(lens))
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    auto, fixed = (Plan(*layer, split_tokens=sp, queries_per_seq=Q) for sp in (0, 256))
+    pages = -(-top // 64)
+    pool = rnd(B * pages, auto.page_elems).to(torch.bfloat16)
+    table = torch.randperm(B * pages, generator=g, device="cuda").to(torch.int32).view(B, pages)
+    args = (rnd(B, Q, 8, 64), pool, table, torch.tensor(lens, dtype=torch.int32, device="cuda"), top,
+            (rnd(auto.key_factor_elems) / 8).to(torch.bfloat16), (rnd(144, 256) / 16).to(torch.bfloat16))
+    a, b, again = decode(auto, *args), decode(fixed, *args), decode(auto, *args)
+    assert torch.equal(a, again)                              # bitwise repeatable
+    assert torch.isfinite(a).all()
+    # the splits change the order of fp32 sums and which rounding a bf16 weight
+    # gets (2^-9 of a row's largest value at most, each way)
+    scale = b.abs().amax(dim=-1, keepdim=True).clamp_min(1e-30)
+    assert float(((a - b).abs() / scale).max()) <= 2.0 ** -7
+    for s, n in enumerate(lens):
+        if n == 0:
+            assert float(a[s].abs().max()) == 0
+
+
 # each kernel of the append at the edges of its tiles: 1 to 32 tokens (one and
 # two 16-token tiles), then enough tokens over 2933 columns for 64 x 64, 128 x
 # 64, 128 x 128 and 128 x 256 tiles, none of the counts a multiple of a tile;
