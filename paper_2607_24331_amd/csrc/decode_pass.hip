@@ -1112,6 +1112,161 @@ __global__ __launch_bounds__(1024) void upproj_wide(const float* __restrict__ am
 }
 
 // ---------------------------------------------------------------------------
+// Up-projection in one round trip: o[row][c] = sum_r a[row][r] R_v[r][kv d_h +
+// c] for 16 rows of one KV head and 32 columns.  Sixteen waves split the
+// ranks; a wave has its whole share in flight at once (at most four 32-rank
+// steps: 8 KB of R_v by the loads' LDS path, 64-byte pieces of rank rows, and
+// its 16 merged rows in operand order in registers), waits for it alone, and
+// multiplies.  R_v lies rank-major and the contraction runs over ranks, so the
+// B operand is read through the transposing LDS load: lane group lq takes
+// ranks 4 lq .. +3 and 16 + 4 lq .. +3 of a step (the A operand the same
+// ranks), the 32-byte halves of a 64-byte row swapped by (row / 4) % 2 so that
+// the eight rows half a wave reads at once fall in distinct banks.  The merged
+// rows are fp32, taken as bf16 hi + lo parts.  The waves' sums are added in
+// wave order through LDS.  A value rank above 2048 takes further rounds.
+// Work-groups of one KV head share an XCD (ids equal mod 8): its row tiles
+// read the same R_v and its column tiles the same merged rows.
+typedef short short4_t __attribute__((ext_vector_type(4)));
+constexpr int kUpWaves = 16;
+constexpr int kUpSteps = 4;                    // 32-rank steps a wave a round
+
+__device__ __forceinline__ void load_lds16(const bf16* g, unsigned char* p) {
+  __builtin_amdgcn_global_load_lds(g, p, 16, 0, 0);
+}
+
+// Two column tiles' operands of one step: p0 and p1 address this lane's pieces
+// of ranks 0..15 (1 KB on: ranks 16..31).  Written out, with a wait of its own,
+// since the compiler waits for every load in flight before such a load.
+__device__ __forceinline__ void read_step(u32x4 (&f)[2], uint32_t p0, uint32_t p1) {
+  uint2 t0 = {}, t1 = {}, t2 = {}, t3 = {};
+#ifdef __HIP_DEVICE_COMPILE__                  // the host pass knows no vector registers
+  uint64_t r0, r1, r2, r3;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:1024\n\t"
+      "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:1024\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+      : "v"(p0), "v"(p1)
+      : "memory");
+  t0 = __builtin_bit_cast(uint2, r0);
+  t1 = __builtin_bit_cast(uint2, r1);
+  t2 = __builtin_bit_cast(uint2, r2);
+  t3 = __builtin_bit_cast(uint2, r3);
+#endif
+  f[0] = u32x4{t0.x, t0.y, t1.x, t1.y};
+  f[1] = u32x4{t2.x, t2.y, t3.x, t3.y};
+}
+
+__global__ __launch_bounds__(kUpWaves * 64) void upproj_tr(const float* __restrict__ amerged,
+                                                           const bf16* __restrict__ Rv,
+                                                           float* __restrict__ out, int rows, int rv,
+                                                           HeadTables tb) {
+  __shared__ __align__(1024) unsigned char smem[kUpWaves * kUpSteps * 2048];
+  const int nct = tb.head_dim / 32, nrt = (rows + 15) / 16;
+  const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+  const int kv = 8 * (pos / (nct * nrt)) + xcd, in = pos % (nct * nrt);
+  if (kv >= tb.n_kv_heads) return;
+  const int ct = in % nct, row0 = 16 * (in / nct);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  const int dh = tb.head_dim, n = tb.n_kv_heads * dh, qpk = tb.q_per_kv;
+  const int nstep = (rv + 31) >> 5;
+  const int s0 = w * nstep / kUpWaves, s1 = (w + 1) * nstep / kUpWaves;
+  // this lane's A row (clamped; results of rows past the end are dropped)
+  const int crow = min(row0 + lr, rows - 1);
+  const float* arow = amerged + (int64_t(crow / qpk) * tb.n_q_heads + kv * qpk + crow % qpk) * rv;
+  // loads: lane: rank lane / 4 of sixteen, 16-byte LDS piece lane % 4, which
+  // holds global piece (lane % 4) ^ 2 (rank / 4 % 2)
+  const int lrank = lane >> 2, gp = (lane & 3) ^ (2 * ((lane >> 4) & 1));
+  const bf16* src = Rv + kv * dh + 32 * ct + 8 * gp;
+  unsigned char* mine = smem + w * (kUpSteps * 2048);
+  const uint32_t base =
+      uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)(mine)));
+  const uint32_t at = (4 * lq + (lr >> 2)) * 64 + 8 * (lr & 3);
+  const uint32_t p0 = base + at + 32 * (lq & 1), p1 = base + at + 32 * (1 - (lq & 1));
+  floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+  const bool vec = (rv & 3) == 0;              // 16-byte aligned rows
+  for (int sb = s0; sb < s1; sb += kUpSteps) {
+    const int ns = min(kUpSteps, s1 - sb);
+    // unconditional loads at clamped ranks; ranks past r_v meet zero rows of a
+    // zeroed R_v (below)
+#pragma unroll
+    for (int k = 0; k < kUpSteps; ++k)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const int r = min(32 * (sb + min(k, ns - 1)) + 16 * hf + lrank, rv - 1);
+        load_lds16(src + int64_t(r) * n, mine + k * 2048 + hf * 1024);
+      }
+    float4 av[kUpSteps][2];
+#pragma unroll
+    for (int k = 0; k < kUpSteps; ++k)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const int r = 32 * (sb + min(k, ns - 1)) + 16 * hf + 4 * lq;
+        if (vec) {
+          av[k][hf] = *reinterpret_cast<const float4*>(arow + min(r, rv - 4));
+          if (r >= rv) av[k][hf] = make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+          float t[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) t[j] = r + j < rv ? arow[r + j] : 0.f;
+          av[k][hf] = make_float4(t[0], t[1], t[2], t[3]);
+        }
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wave's share is in LDS
+    if (32 * (sb + ns) > rv) {                                   // the ranks past r_v, as zeros
+      const int z = rv - 32 * (sb + ns - 1);                     // ranks of the last step
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+        if (16 * hf + lrank >= z)
+          *reinterpret_cast<u32x4*>(mine + (ns - 1) * 2048 + hf * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+#pragma unroll
+    for (int k = 0; k < kUpSteps; ++k) {
+      if (k >= ns) break;
+      u32x4 B[2];
+      read_step(B, p0 + k * 2048, p1 + k * 2048);
+      const float f[8] = {av[k][0].x, av[k][0].y, av[k][0].z, av[k][0].w,
+                          av[k][1].x, av[k][1].y, av[k][1].z, av[k][1].w};
+      u32x4 hi, lo;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bf16 h0 = static_cast<bf16>(f[2 * j]), h1 = static_cast<bf16>(f[2 * j + 1]);
+        const bf16 l0 = static_cast<bf16>(f[2 * j] - static_cast<float>(h0));
+        const bf16 l1 = static_cast<bf16>(f[2 * j + 1] - static_cast<float>(h1));
+        hi[j] = uint32_t(__builtin_bit_cast(uint16_t, h0)) | (uint32_t(__builtin_bit_cast(uint16_t, h1)) << 16);
+        lo[j] = uint32_t(__builtin_bit_cast(uint16_t, l0)) | (uint32_t(__builtin_bit_cast(uint16_t, l1)) << 16);
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        acc[c] = mfma(hi, B[c], acc[c]);
+        acc[c] = mfma(lo, B[c], acc[c]);
+      }
+    }
+  }
+  __syncthreads();                             // every wave has read its share
+  floatx4* red = reinterpret_cast<floatx4*>(smem);               // [wave][2][64]
+#pragma unroll
+  for (int c = 0; c < 2; ++c) red[(w * 2 + c) * 64 + lane] = acc[c];
+  __syncthreads();
+  if (tid < 512) {                             // (column tile, row, column) of 16 rows x 32 columns
+    const float* rf = reinterpret_cast<const float*>(smem);
+    const int c = tid >> 8, r = (tid >> 4) & 15, col = tid & 15;
+    const int e = c * 256 + ((r >> 2) * 16 + col) * 4 + (r & 3);
+    float t = rf[e];
+#pragma unroll
+    for (int k = 1; k < kUpWaves; ++k) t += rf[k * 512 + e];
+    const int row = row0 + r;
+    if (row < rows) {
+      const int bb = row / qpk, h = kv * qpk + row % qpk;
+      out[(int64_t(bb) * tb.n_q_heads + h) * dh + 32 * ct + 16 * c + col] = t;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Up-projection on MFMA: o[row][c] = sum_r a[row][r] R_v[r][kv d_h + c] for
 // the rows of one KV head (sequence, query, head of the KV head).  One
 // work-group of W waves (4, or 8 when a wave would otherwise walk 32 rank
@@ -1412,6 +1567,16 @@ size_t upproj_wide_lds_bytes(const dckv_plan& p, int rows, int rb) {
 hipError_t launch_upproj(const dckv_plan& p, int32_t batch_rows, const float* amerged,
                          const void* R_value, float* out, hipStream_t stream) {
   const int rows = batch_rows * p.qpk;          // rows a KV head
+  // from three rows on and a long contraction: the one-round-trip kernel
+  // (32 KV heads of 128, r_v 2048: 4 rows 13.2 -> 9.9 us, 8 rows 12.7 -> 9.8;
+  // r_v 1536, 64 rows 24.2 -> 21.3; with 8 KV heads, r_v 768, 16 rows, its
+  // few large work-groups start later than they save: 6.7 -> 8.7)
+  if (rows >= 3 && p.rv >= 1024 && p.dh % 32 == 0) {
+    const int per = (p.dh / 32) * ((rows + 15) / 16);
+    hipLaunchKernelGGL(upproj_tr, dim3(8 * ((p.Hkv + 7) / 8) * per), dim3(kUpWaves * 64), 0, stream,
+                       amerged, static_cast<const bf16*>(R_value), out, rows, p.rv, p.tables);
+    return hipGetLastError();
+  }
   // one or two rows a KV head, with 64-column tiles that give the grid at
   // least 32 work-groups: the wide kernel (whole 128-byte pieces of R_v;
   // from three rows on its per-lane products cost more than the MFMA

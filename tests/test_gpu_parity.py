@@ -352,6 +352,23 @@ def test_append_random_within_one_ulp():
         assert np.all(Zg[5] == 0)        # skipped slot untouched
 
 
+# the one-round-trip up-projection (three rows a KV head or more, value ranks
+# from 1024 on): ranks not a multiple of 4 or 32, above one round of 2048, rows
+# at the edges of 16-row tiles, KV heads not a multiple of 8
+@pytest.mark.parametrize("rv, batch, kv", [(1027, 3, 17), (1040, 17, 9), (1500, 33, 12), (2500, 4, 20)])
+def test_upproject_edges(rv, batch, kv):
+    lens = tuple(1 + (29 * i) % 97 for i in range(batch))
+    wl = custom_workload(name="up", seed=rv, hidden=2560, num_q_heads=kv, num_kv_heads=kv, head_dim=128,
+                         group_of_kv=tuple(i % 2 for i in range(kv)), group_rank=(40, 72),
+                         value_rank=rv, dtype="bf16", batch=batch, seq_lens=lens)
+    inp = make_inputs(wl)
+    plan = plan_for(wl)
+    out = run_decode(inp, plan, gpu_pool_with_append(inp, plan))
+    pairs = [(b, h) for b in (0, batch // 2, batch - 1) for h in (0, kv // 2, kv - 1)]
+    errs = [row_rel_err(out[b, h], o) for (b, h), o in oracle_rows(inp, pairs).items()]
+    assert max(errs) <= TOL_REL_ROW
+
+
 # balanced splits: a short and a long sequence, empty ones, equal lengths,
 # lengths beyond max_context, as many sequences as one wave cuts (256) and one
 # more (fixed splits), several queries (two row slices)
