@@ -362,7 +362,7 @@ static DecodeShape pass_shape(const dckv_plan& p, int32_t batch, int32_t max_con
   return s;
 }
 
-DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context) {
+DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context, bool plain) {
   // The two-pass kernels when asked for, when the single-pass kernel does not
   // apply, or when it would cut the rows into several slices (a value rank
   // beyond what one slice's accumulators hold), each slice reading the whole
@@ -381,11 +381,24 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context)
   s.max_context = max_context;
   s.mfma = p.mfma_ok;
   int64_t L = p.split_tokens;
+  // Two value slices where a compute unit's share is at most three pages: a
+  // split's partials (value rank x rows fp32, whatever its length) are then
+  // most of the traffic beside the latents, and twice the splits' length
+  // halves them, the keys, which both halves read, coming the second time
+  // from their XCD's L2.  Measured, 8 sequences, one slice / two, us: value
+  // rank 2048: 512 tokens 46.8 / 41.7, 2048: 67.2 / 59.6, 4096: 89.9 / 86.3,
+  // 6144: 111.5 / 108.9, 8192: 133.0 / 132.7, 16384: 216 / 223; 1536: 39.2 /
+  // 35.8, 53.4 / 47.7, 70.1 / 64.9, 84.1 / 83.2, 98.1 / 99.6, 153 / 163.
+  if (s.mfma && L == 0 && p.mfma2_ok && !plain) {
+    const int64_t npm = (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS;
+    s.halves = int64_t(batch) * npm * p.mfma.n_slices <= 3 * kTargetWorkgroups;
+  }
+  const int vs = s.halves ? 2 : 1;
   if (L == 0) {
     if (s.mfma) {
       // about one work-group per compute unit over the whole batch, at most
       // the split kernel's page-list capacity
-      const int64_t tokens = int64_t(batch) * max_context * p.mfma.n_slices;
+      const int64_t tokens = int64_t(batch) * max_context * p.mfma.n_slices * vs;
       L = (tokens + kTargetWorkgroups - 1) / kTargetWorkgroups;
       L = std::max<int64_t>(DCKV_PAGE_TOKENS, (L + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS * DCKV_PAGE_TOKENS);
       L = std::min<int64_t>(L, mfma_max_split_tokens());
@@ -423,11 +436,11 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context)
     // compute units without work (split kernel 370 us, balanced 292; the
     // record's load before all others costs equal lengths 0.7 us of 88); one
     // sequence is cut evenly as it is.
-    if (p.split_tokens == 0 && batch >= 2 && batch <= kSchedMaxBatch && units <= kSchedMaxUnits &&
+    if (!plain && p.split_tokens == 0 && batch >= 2 && batch <= kSchedMaxBatch && units <= kSchedMaxUnits &&
         (p.dh == 64 || p.dh == 128)) {
       const int64_t npm = (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS;
       const int64_t cap = mfma_max_split_tokens() / DCKV_PAGE_TOKENS;
-      const int64_t target = std::max<int64_t>(1, kTargetWorkgroups / p.mfma.n_slices);
+      const int64_t target = std::max<int64_t>(1, kTargetWorkgroups / (p.mfma.n_slices * vs));
       int64_t U = units;
       const int64_t whole = U / target * target;
       if (whole >= batch && int64_t(batch) * ((npm + cap - 1) / cap) <= whole) U = whole;

@@ -388,8 +388,9 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
 
   const int J = mt.n_slices;
   const int Lid = blockIdx.x;
-  const int grp = Lid / (8 * J), rr = Lid % (8 * J);
-  const int slice = rr / 8;
+  const int JV = J * mt.vs;
+  const int grp = Lid / (8 * JV), rr = Lid % (8 * JV);
+  const int slice = rr / 8 / mt.vs, vh = rr / 8 % mt.vs;   // vh: value slice
   const int u = grp * 8 + (rr % 8);       // all slices of unit u share an XCD (ids equal mod 8)
   if (u >= n_units) return;               // n_units = batch * n_split, or the balanced splits (the grid is padded)
   // fixed splits: sequence and first page by number; balanced ones (SCHED) by
@@ -463,8 +464,8 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   // last key block's change of length is on every wave's schedule
   const int NK = KR == VR ? (nk_real + KR - 1) / KR * KR : max(KR, (nk_real + KR - 1) / KR * KR);
   const int pair0_w = (n_w == 0) ? 0 : nch0;
-  const int mt0_w = w * mt.mtw;
-  const int mcnt_w = max(0, min(mt.mtw, mt.mt_v - mt0_w));
+  const int mt0_w = vh * mt.vt + w * mt.mtw;
+  const int mcnt_w = max(0, min(mt.mtw, min(mt.mt_v, (vh + 1) * mt.vt) - mt0_w));
   // only the last chunk of the key latent can hold columns beyond r; its
   // list position in this tile, or -1
   const int kc_last = (RK - 1) / 32;
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
 
   // ---- partials: (m[NH], l[NH]) compact per split, acc[rank][NH] (head slot fastest)
   const int64_t prow = SCHED ? int64_t(slice) * n_units + u : (int64_t(b) * J + slice) * n_split + split;
-  if (w == 0 && lane < 16) {
+  if (w == 0 && vh == 0 && lane < 16) {
     float* pml = part_ml + prow * (2 * NH);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -998,7 +999,7 @@ __global__ __launch_bounds__(256) void merge_mfma(const float* __restrict__ part
 }
 
 template <int W, int NT, int MTW, int KR>
-hipError_t launch_split(const dckv_plan& p, const DecodeShape& sh, const u32x4* qblk,
+hipError_t launch_split(const dckv_plan& p, const MfmaTables& mt, const DecodeShape& sh, const u32x4* qblk,
                         const void* pool, int64_t num_pages, const int32_t* page_table,
                         int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
                         size_t lds, hipStream_t stream, const bf16* pw = nullptr,
@@ -1009,10 +1010,10 @@ hipError_t launch_split(const dckv_plan& p, const DecodeShape& sh, const u32x4* 
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(kern, dim3(sh.n_units * p.mfma.n_slices), dim3(W * 64), lds, stream, qblk,
+      hipLaunchKernelGGL(kern, dim3(sh.n_units * mt.n_slices * mt.vs), dim3(W * 64), lds, stream, qblk,
                          static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
                          sh.max_context, sh.split_tokens, sh.n_split, sh.batch * sh.n_split,
-                         p.RK, p.rv, p.page_elems, p.value_base, part_ml, part, p.mfma, pw,
+                         p.RK, p.rv, p.page_elems, p.value_base, part_ml, part, mt, pw,
                          static_cast<const SchedUnit*>(nullptr));
       return hipGetLastError();
     }
@@ -1022,51 +1023,51 @@ hipError_t launch_split(const dckv_plan& p, const DecodeShape& sh, const u32x4* 
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
-  const int grid = sh.n_units * p.mfma.n_slices;
+  const int grid = sh.n_units * mt.n_slices * mt.vs;
   const int n_units = sched ? sh.n_sched : sh.batch * sh.n_split;
   if (p.prof_before && p.prof_after)   // events stamped by the kernel's own dispatch
     hipExtLaunchKernelGGL(kern, dim3(grid), dim3(W * 64), uint32_t(lds), stream, p.prof_before,
                           p.prof_after, 0u, qblk, static_cast<const bf16*>(pool), num_pages,
                           page_table, max_pages, seq_lens, sh.max_context, sh.split_tokens,
                           sh.n_split, n_units, p.RK, p.rv, p.page_elems,
-                          p.value_base, part_ml, part, p.mfma, static_cast<const bf16*>(nullptr),
+                          p.value_base, part_ml, part, mt, static_cast<const bf16*>(nullptr),
                           sched);
   else
     hipLaunchKernelGGL(kern, dim3(grid), dim3(W * 64), lds, stream, qblk,
                        static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
                        sh.max_context, sh.split_tokens, sh.n_split, n_units, p.RK,
-                       p.rv, p.page_elems, p.value_base, part_ml, part, p.mfma,
+                       p.rv, p.page_elems, p.value_base, part_ml, part, mt,
                        static_cast<const bf16*>(nullptr), sched);
   return hipGetLastError();
 }
 
 template <int W, int NT, int MTW>
-hipError_t launch_split_r(const dckv_plan& p, const DecodeShape& sh, const u32x4* qt,
+hipError_t launch_split_r(const dckv_plan& p, const MfmaTables& mt, const DecodeShape& sh, const u32x4* qt,
                           const void* pool, int64_t num_pages, const int32_t* page_table,
                           int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
                           size_t lds, hipStream_t stream, const SchedUnit* sched) {
   if constexpr (MTW <= 12) {               // the plan mixes block sizes only here
-    if (p.mfma.ring == 12)
-      return launch_split<W, NT, MTW, 12>(p, sh, qt, pool, num_pages, page_table, max_pages,
+    if (mt.ring == 12)
+      return launch_split<W, NT, MTW, 12>(p, mt, sh, qt, pool, num_pages, page_table, max_pages,
                                           seq_lens, part_ml, part, lds, stream, nullptr, sched);
-    if (p.mfma.ring == 14)
-      return launch_split<W, NT, MTW, 14>(p, sh, qt, pool, num_pages, page_table, max_pages,
+    if (mt.ring == 14)
+      return launch_split<W, NT, MTW, 14>(p, mt, sh, qt, pool, num_pages, page_table, max_pages,
                                           seq_lens, part_ml, part, lds, stream, nullptr, sched);
   }
-  if (p.mfma.ring != 16) return hipErrorInvalidValue;
-  return launch_split<W, NT, MTW, 16>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens,
+  if (mt.ring != 16) return hipErrorInvalidValue;
+  return launch_split<W, NT, MTW, 16>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, seq_lens,
                                       part_ml, part, lds, stream, nullptr, sched);
 }
 
 template <int W, int NT>
-hipError_t launch_split_w(const dckv_plan& p, const DecodeShape& sh, const u32x4* qt,
+hipError_t launch_split_w(const dckv_plan& p, const MfmaTables& mt, const DecodeShape& sh, const u32x4* qt,
                           const void* pool, int64_t num_pages, const int32_t* page_table,
                           int32_t max_pages, const int32_t* seq_lens, float* part_ml, float* part,
                           size_t lds, hipStream_t stream, const SchedUnit* sched) {
 #define DCKV_SPLIT(M)                                                                   \
-  return launch_split_r<W, NT, M>(p, sh, qt, pool, num_pages, page_table, max_pages, \
+  return launch_split_r<W, NT, M>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, \
                                   seq_lens, part_ml, part, lds, stream, sched)
-  switch (p.mfma.mtw_t) {
+  switch (mt.mtw_t) {
     case 6: DCKV_SPLIT(6);
     case 8: DCKV_SPLIT(8);
     case 12: DCKV_SPLIT(12);
@@ -1084,11 +1085,12 @@ hipError_t launch_split_pw(const dckv_plan& p, const DecodeShape& sh, const void
                            int64_t num_pages, const int32_t* page_table, int32_t max_pages,
                            const int32_t* seq_lens, float* part_ml, float* part, const bf16* pw,
                            size_t lds, hipStream_t stream) {
+  const MfmaTables& mt = p.mfma;
 #define DCKV_PW(M)                                                                             \
   return launch_split<W, NT, M, ((2 * (M)) % 16 == 0 ? 16 : 12)>(                              \
-      p, sh, nullptr, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, \
+      p, mt, sh, nullptr, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, \
       stream, pw)
-  switch (p.mfma.mtw_t) {
+  switch (mt.mtw_t) {
     case 6: DCKV_PW(6);
     case 8: DCKV_PW(8);
     case 12: DCKV_PW(12);
@@ -1101,7 +1103,7 @@ hipError_t launch_split_pw(const dckv_plan& p, const DecodeShape& sh, const void
 
 // Merge of the splits' partials and the up-projection by R_v, shared by the
 // position-free and the rotary decode.
-hipError_t launch_merge_upproj(const dckv_plan& p, const DecodeShape& sh, const int32_t* seq_lens,
+hipError_t launch_merge_upproj(const dckv_plan& p, const MfmaTables& mt, const DecodeShape& sh, const int32_t* seq_lens,
                                const float* part_ml, const float* part, float* amerged,
                                const void* R_value, float* out, hipStream_t stream,
                                const SchedSeq* seqs = nullptr) {
@@ -1111,12 +1113,12 @@ hipError_t launch_merge_upproj(const dckv_plan& p, const DecodeShape& sh, const 
 #define DCKV_MERGE(NH, MR)                                                                      \
   (seqs ? (lng ? merge_mfma<NH, true, MR, true> : merge_mfma<NH, false, MR, true>)              \
         : (lng ? merge_mfma<NH, true, MR, false> : merge_mfma<NH, false, MR, false>))
-  auto kern = sh.merge_ranks == 16 ? (p.mfma.nt == 1 ? DCKV_MERGE(16, 16) : DCKV_MERGE(32, 16))
-                                   : (p.mfma.nt == 1 ? DCKV_MERGE(16, 8) : DCKV_MERGE(32, 8));
+  auto kern = sh.merge_ranks == 16 ? (mt.nt == 1 ? DCKV_MERGE(16, 16) : DCKV_MERGE(32, 16))
+                                   : (mt.nt == 1 ? DCKV_MERGE(16, 8) : DCKV_MERGE(32, 8));
 #undef DCKV_MERGE
-  hipLaunchKernelGGL(kern, dim3(sh.batch * p.mfma.n_slices, sh.n_rchunks), dim3(256), 0, stream,
+  hipLaunchKernelGGL(kern, dim3(sh.batch * mt.n_slices, sh.n_rchunks), dim3(256), 0, stream,
                      part_ml, part, seq_lens, sh.max_context, sh.split_tokens,
-                     seqs ? sh.n_sched : sh.n_split, p.rv, amerged, p.tables, p.mfma, seqs);
+                     seqs ? sh.n_sched : sh.n_split, p.rv, amerged, p.tables, mt, seqs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_upproj(p, sh.batch * p.Q, amerged, R_value, out, stream);
@@ -1159,6 +1161,7 @@ hipError_t launch_decode_mfma(const dckv_plan& p, const DecodeShape& sh, const f
                               const void* pool, int64_t num_pages, const int32_t* page_table,
                               int32_t max_pages, const int32_t* seq_lens, const void* R_keys,
                               const void* R_value, float* out, void* workspace, hipStream_t stream) {
+  const MfmaTables& mt = sh.halves ? p.mfma2 : p.mfma;
   char* ws = static_cast<char*>(workspace);
   u32x4* qt = reinterpret_cast<u32x4*>(ws + sh.off_qt);
   float* part_ml = reinterpret_cast<float*>(ws + sh.off_ml);
@@ -1173,18 +1176,18 @@ hipError_t launch_decode_mfma(const dckv_plan& p, const DecodeShape& sh, const f
     sa.units = reinterpret_cast<SchedUnit*>(ws + sh.off_sched);
     sa.seqs = reinterpret_cast<SchedSeq*>(sa.units + sh.n_sched);
   }
-  hipError_t e = launch_fold(p, p.mfma, sh.batch, q, R_keys, qt, sa, stream);
+  hipError_t e = launch_fold(p, mt, sh.batch, q, R_keys, qt, sa, stream);
   if (e != hipSuccess) return e;
-  if (p.mfma.waves == 4)
-    e = p.mfma.nt == 1
-            ? launch_split_w<4, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
-            : launch_split_w<4, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
+  if (mt.waves == 4)
+    e = mt.nt == 1
+            ? launch_split_w<4, 1>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
+            : launch_split_w<4, 2>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
   else
-    e = p.mfma.nt == 1
-            ? launch_split_w<8, 1>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
-            : launch_split_w<8, 2>(p, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
+    e = mt.nt == 1
+            ? launch_split_w<8, 1>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units)
+            : launch_split_w<8, 2>(p, mt, sh, qt, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, lds, stream, sa.units);
   if (e != hipSuccess) return e;
-  return launch_merge_upproj(p, sh, seq_lens, part_ml, part, amerged, R_value, out, stream, sa.seqs);
+  return launch_merge_upproj(p, mt, sh, seq_lens, part_ml, part, amerged, R_value, out, stream, sa.seqs);
 }
 
 size_t rope_value_lds_bytes(const dckv_plan& p, int32_t split_tokens) {
@@ -1219,7 +1222,7 @@ hipError_t launch_decode_rope(const dckv_plan& p, const DecodeShape& sh, const f
             ? launch_split_pw<8, 1>(p, sh, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, pw, lds, stream)
             : launch_split_pw<8, 2>(p, sh, pool, num_pages, page_table, max_pages, seq_lens, part_ml, part, pw, lds, stream);
   if (e != hipSuccess) return e;
-  return launch_merge_upproj(p, sh, seq_lens, part_ml, part, amerged, R_value, out, stream);
+  return launch_merge_upproj(p, p.mfma, sh, seq_lens, part_ml, part, amerged, R_value, out, stream);
 }
 
 }  // namespace dckv

@@ -47,7 +47,9 @@ struct MfmaTables {
   int32_t nt;                              // 16-head MFMA tiles per slice (1 or 2)
   int32_t mt_v;                            // value M-tiles: ceil(r_v / 16)
   int32_t waves;                           // waves a work-group: 4 or 8
-  int32_t mtw;                             // value M-tiles per wave: ceil(mt_v / waves)
+  int32_t vs;                              // value slices (1 or 2) that separate work-groups serve
+  int32_t vt;                              // value M-tiles a value slice: ceil(mt_v / vs)
+  int32_t mtw;                             // value M-tiles per wave: ceil(vt / waves)
   int32_t mtw_t;                           // compiled tile capacity: 6, 8, 12, 16 or 32 >= mtw
   int32_t ring;                            // key block: loads in flight a wave (12, 14 or 16)
   int32_t max_pairs;                       // most LDS query blocks of any slice
@@ -85,6 +87,7 @@ struct DecodeShape {
   int32_t n_split;          // ceil(max_context / split_tokens), at least 1
   bool mfma;                // bf16 single-pass MFMA path (split_mfma)
   bool pass;                // bf16 two-pass MFMA path (score_pages, value_pages)
+  bool halves;              // single-pass path in two value slices (plan.mfma2)
   int32_t n_units;          // batch * n_split rounded up to a multiple of 8: grid units (MFMA path)
   int32_t n_rchunks;        // value-rank chunks of the merge (MFMA path)
   int32_t merge_ranks = 8;  // value ranks a merge work-group (8 or 16)
@@ -153,6 +156,8 @@ struct dckv_plan {
   dckv::HeadTables tables;
   bool mfma_ok = false;              // bf16 single-pass MFMA decode path applies
   dckv::MfmaTables mfma{};
+  bool mfma2_ok = false;             // it may also run in two value slices:
+  dckv::MfmaTables mfma2{};          // mfma's rows and key chunks, half the value tiles a wave
   bool pass_ok = false;              // bf16 two-pass decode applies (<= 256 (query, head) rows)
   dckv::MfmaTables pass{};           // its tables: slices of <= 32 rows, fewest chunk loads
   int32_t pass_ring = 0;             // score-pass loads in flight a wave (16; 32 measured slower)
@@ -230,7 +235,8 @@ hipError_t launch_decode_rope(const dckv_plan& p, const DecodeShape& sh, const f
                               hipStream_t stream);
 
 // Defined in the kernel sources.
-DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context);
+// plain: fixed splits and one value slice (the rotary decode's)
+DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context, bool plain = false);
 DenseShape dense_shape(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t batch,
                        int32_t max_context, int32_t split_tokens);
 hipError_t launch_dense_decode(const DenseShape& sh, const float* q, const void* pool,

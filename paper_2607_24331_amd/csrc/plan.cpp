@@ -109,6 +109,7 @@ int32_t padded_items(const MfmaTables& t, int32_t ring) {
 
 void build_mfma_tables(dckv_plan& p) {
   p.mfma_ok = false;
+  p.mfma2_ok = false;
   p.mfma = MfmaTables{};
   if (p.dtype != DCKV_BF16) return;
   if (p.dh % 8 != 0) return;                   // the up-projection reads 8 columns at a time
@@ -122,6 +123,8 @@ void build_mfma_tables(dckv_plan& p) {
   // beyond 128 a lane, a default slicing takes twice the slices (16 rows a
   // slice), each slice then reading the value part on its own.
   t.waves = p.decode_waves ? p.decode_waves : (t.mt_v >= 8 ? 8 : 4);
+  t.vs = 1;
+  t.vt = t.mt_v;
   t.mtw = (t.mt_v + t.waves - 1) / t.waves;
   if (p.head_slices == 0) {
     while (J < kMaxSlices && J < nrows && ((nrows + J - 1) / J + 15) / 16 * t.mtw > 32) J *= 2;
@@ -180,6 +183,27 @@ void build_mfma_tables(dckv_plan& p) {
   const int64_t lds = int64_t(t.max_pairs) * 2048 + 32 * 72 * 2 + 2 * 8 * 32 * 4 + 256 * 4;
   if (lds > 160 * 1024) return;
   p.mfma_ok = true;
+
+  // The same rows and key chunks with the value tiles in two halves, where a
+  // wave then still has six tiles, the smallest capacity that is compiled
+  // (fewer would be padded up to it).
+  MfmaTables h = t;
+  h.vs = 2;
+  h.vt = (t.mt_v + 1) / 2;
+  h.mtw = (h.vt + h.waves - 1) / h.waves;
+  if (p.decode_waves || h.waves != 8 || h.mtw < 6) return;
+  for (int32_t c : {6, 8, 12, 16})
+    if (h.mtw <= c) {
+      h.mtw_t = c;
+      break;
+    }
+  h.ring = 0;
+  for (int32_t ring : {16, 14, 12}) {
+    if (h.mtw_t >= 16 && ring != 16) continue;
+    if (h.ring == 0 || padded_items(h, ring) < padded_items(h, h.ring)) h.ring = ring;
+  }
+  p.mfma2 = h;
+  p.mfma2_ok = true;
 }
 
 // Tables of the two-pass decode: the (query, head) rows in J = ceil(rows / 32)

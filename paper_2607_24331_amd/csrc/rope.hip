@@ -654,9 +654,7 @@ __global__ __launch_bounds__(512, 1) void rope_scores_res(
 }  // namespace
 
 DecodeShape rope_shape(const dckv_plan& p, int32_t batch, int32_t max_context) {
-  DecodeShape s = decode_shape(p, batch, max_context);
-  s.n_sched = 0;                            // fixed splits: the weights' rows are theirs
-  s.sched_bytes = 0;
+  DecodeShape s = decode_shape(p, batch, max_context, true);   // the weights' rows are fixed splits'
   // the split's scores and weights live in LDS: at most kRopeMaxSplit tokens
   int64_t L = std::min<int64_t>(s.split_tokens, kRopeMaxSplit);
   s.split_tokens = int32_t(L);

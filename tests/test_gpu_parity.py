@@ -369,6 +369,38 @@ def test_upproject_edges(rv, batch, kv):
     assert max(errs) <= TOL_REL_ROW
 
 
+# short splits in two value slices: value ranks whose halves are not whole tiles
+# a wave (11 tiles of 16 and a rest), one and two 16-row tiles, several queries
+# (row and value slices), one sequence and several, against the oracle
+@pytest.mark.parametrize("rv, heads, lens, Q", [(1411, 32, (700,), 1), (1411, 12, (130, 1, 517), 1),
+                                                (2048, 32, (64, 300), 2)])
+def test_value_halves(rv, heads, lens, Q):
+    from paper_2607_24331_amd import Plan, decode
+    wl = custom_workload(name="halves", seed=rv + heads, hidden=2048, num_q_heads=heads,
+                         num_kv_heads=heads, head_dim=128 if heads < 32 else 64,
+                         group_of_kv=tuple(i % 3 for i in range(heads)), group_rank=(50, 61, 70),
+                         value_rank=rv, dtype="bf16", batch=len(lens), seq_lens=lens)
+    inp = make_inputs(wl)
+    plan = Plan(wl.hidden, heads, heads, wl.head_dim, wl.group_of_kv, wl.group_rank, rv,
+                queries_per_seq=Q)
+    pool = gpu_pool_with_append(inp, plan)
+    q = np.random.default_rng(2).standard_normal((len(lens), Q, heads, wl.head_dim)).astype(np.float32)
+    args = (torch.from_numpy(q).cuda(), pool, torch.from_numpy(inp.page_table).cuda(),
+            torch.from_numpy(inp.seq_lens).cuda(), max(lens), dev(inp.R_keys_flat, "bf16"),
+            dev(inp.R_value, "bf16"))
+    out = decode(plan, *args)
+    assert torch.equal(out, decode(plan, *args))
+    got = out.cpu().numpy().astype(np.float64)
+    ref = oattn.decode_multi(q, oracle_pool(inp), inp.page_table, wl.seq_lens, inp.R_blocks,
+                             inp.R_value, book_for(wl), chunk=None)
+    errs = []
+    for b in range(len(lens)):
+        for i in range(Q):
+            if oattn.visible_tokens(lens[b], Q, i):
+                errs += [row_rel_err(got[b, i, h], ref[b, i, h]) for h in range(heads)]
+    assert max(errs) <= TOL_REL_ROW
+
+
 # balanced splits: a short and a long sequence, empty ones, equal lengths,
 # lengths beyond max_context, as many sequences as one wave cuts (256) and one
 # more (fixed splits), several queries (two row slices)
