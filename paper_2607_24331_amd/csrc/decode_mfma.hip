@@ -174,15 +174,16 @@ __device__ __forceinline__ int wave_scan(int v, int lane, bool mx) {   // inclus
 }
 __device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
   constexpr int N = kSchedMaxBatch / 64, M = kSchedMaxUnits / 64;
-  __shared__ int np_lds[kSchedMaxBatch], first[kSchedMaxBatch], owner[kSchedMaxUnits];
+  __shared__ int len_lds[kSchedMaxBatch], first[kSchedMaxBatch], owner[kSchedMaxUnits];
   const int lane = threadIdx.x;
   int np[N], pages = 0;                      // pages < 2^25 a sequence, < 2^17 units of 2^8 in all
 #pragma unroll
   for (int k = 0; k < N; ++k) {
     const int b = lane * N + k;
     const int t = sa.seq_lens[min(b, batch - 1)];
-    np[k] = b < batch ? (max(0, min(t, sa.max_context)) + 63) >> 6 : 0;
-    np_lds[b] = np[k];
+    const int len = b < batch ? max(0, min(t, sa.max_context)) : 0;
+    np[k] = (len + 63) >> 6;
+    len_lds[b] = len;
     pages += np[k];
   }
 #pragma unroll
@@ -194,7 +195,7 @@ __device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
     const int d = L + lane;
     const float inv = 1.f / float(d);
     int n = 0;
-    for (int b = 0; b < batch; ++b) n += ceil_div(np_lds[b], d, inv);
+    for (int b = 0; b < batch; ++b) n += ceil_div((len_lds[b] + 63) >> 6, d, inv);
     const unsigned long long fits = __ballot(n <= sa.n_units);
     if (fits) {
       L += __ffsll(fits) - 1;
@@ -234,8 +235,11 @@ __device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
     SchedUnit e = {0, 0, 0, 0};
     if (u < total) {
       const int b = lane ? max(own[k], prev) : own[k], i = u - first[b];
-      const int n = ceil_div(np_lds[b], L, inv), q = np_lds[b] / n, r = np_lds[b] - q * n;
-      e = SchedUnit{b, i * q + min(i, r), q + (i < r ? 1 : 0), 0};
+      const int len = len_lds[b], pg = (len + 63) >> 6;
+      const int n = ceil_div(pg, L, inv), q = pg / n, r = pg - q * n;
+      const int p0 = i * q + min(i, r);
+      e = SchedUnit{b, p0, min(64 * (q + (i < r ? 1 : 0)), len - 64 * p0),
+                    sa.page_table[int64_t(b) * sa.max_pages + p0]};
     }
     sa.units[u] = e;
   }
@@ -394,11 +398,12 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   const int u = grp * 8 + (rr % 8);       // all slices of unit u share an XCD (ids equal mod 8)
   if (u >= n_units) return;               // n_units = batch * n_split, or the balanced splits (the grid is padded)
   // fixed splits: sequence and first page by number; balanced ones (SCHED) by
-  // the unit's record
+  // the unit's record, which also holds what the first loads of latents need
+  // (the page and the number of tokens), so that they wait for it alone
   SchedUnit un = {0, 0, 0, 0};
   if constexpr (SCHED) {
     un = sched[u];
-    if (un.pages == 0) return;            // fewer splits than units
+    if (un.tokens == 0) return;           // fewer splits than units
   }
   const int b = SCHED ? un.b : u / n_split, split = SCHED ? 0 : u % n_split;
   const int page0 = SCHED ? un.page0 : split * (split_tokens >> 6);
@@ -437,12 +442,12 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
 #pragma unroll
     for (int k = 0; k < kQblkLoads; ++k) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
   }
-  int pid0 = page0 < max_pages ? page_table[int64_t(b) * max_pages + page0] : -1;
+  int pid0 = SCHED ? un.pid : page0 < max_pages ? page_table[int64_t(b) * max_pages + page0] : -1;
   int T_b = seq_lens[b];
   const int t0 = 64 * page0;
   pid0 = __builtin_amdgcn_readfirstlane((pid0 >= 0 && pid0 < num_pages) ? pid0 : -1);
   T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
-  const int t1 = min(SCHED ? t0 + 64 * un.pages : t0 + split_tokens, T_b);
+  const int t1 = SCHED ? t0 + un.tokens : min(t0 + split_tokens, T_b);
   if (t0 >= t1) return;                   // the merge only reads splits holding tokens
   const int np = (t1 - t0 + 63) / 64;
 
@@ -1171,6 +1176,8 @@ hipError_t launch_decode_mfma(const dckv_plan& p, const DecodeShape& sh, const f
   SchedArgs sa{};
   if (sh.n_sched > 0) {
     sa.seq_lens = seq_lens;
+    sa.page_table = page_table;
+    sa.max_pages = max_pages;
     sa.max_context = sh.max_context;
     sa.n_units = sh.n_sched;
     sa.units = reinterpret_cast<SchedUnit*>(ws + sh.off_sched);

@@ -116,10 +116,11 @@ struct DecodeShape {
   size_t bytes;
 };
 
-// Balanced splits: unit u takes pages [page0, page0 + pages) of sequence b
-// (pages 0: nothing); sequence b's units are u0 .. u0 + units - 1.
+// Balanced splits: unit u takes `tokens` tokens of sequence b from page page0
+// on, whose entry in the page table is pid (tokens 0: nothing); sequence b's
+// units are u0 .. u0 + units - 1.
 struct SchedUnit {
-  int32_t b, page0, pages, pad;
+  int32_t b, page0, tokens, pid;
 };
 struct SchedSeq {
   int32_t u0, units;
@@ -130,7 +131,8 @@ constexpr int kSchedMaxUnits = 512;   // eight units a lane
 // What the fold kernel needs to cut them (units null: fixed splits).
 struct SchedArgs {
   const int32_t* seq_lens;
-  int32_t max_context, n_units;
+  const int32_t* page_table;
+  int32_t max_pages, max_context, n_units;
   SchedUnit* units;
   SchedSeq* seqs;
 };
