@@ -9,6 +9,7 @@ paper_2607_24331_amd/libdckv.so.  Always rebuilds every object.
 
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import shutil
 import subprocess
@@ -66,18 +67,21 @@ SANITIZED_LIB = os.path.join(PKG, "libdckv_sanitized.so")
 def build(verbose: bool = False, sanitize: bool = False) -> str:
     hipcc = shutil.which("hipcc") or os.path.join(ROCM, "bin", "hipcc")
     os.makedirs(BUILD, exist_ok=True)
-    objs = []
+    objs, jobs = [], []
     for src in HOST_SOURCES:
         obj = os.path.join(BUILD, src + (".san.o" if sanitize else ".o"))
         flags = HOST_FLAGS + (SANITIZE_FLAGS if sanitize else [])
-        _run(["g++", *flags, "-I", INCLUDE, "-I", CSRC, "-I", os.path.join(ROCM, "include"),
-              "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+        jobs.append(["g++", *flags, "-I", INCLUDE, "-I", CSRC, "-I", os.path.join(ROCM, "include"),
+                     "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     for src in HIP_SOURCES:
         obj = os.path.join(BUILD, src + ".o")
-        _run([hipcc, *HIPCC_FLAGS, *HIPCC_EXTRA.get(src, []), "-I", INCLUDE, "-I", CSRC, "-c",
-              os.path.join(CSRC, src), "-o", obj], verbose)
+        jobs.append([hipcc, *HIPCC_FLAGS, *HIPCC_EXTRA.get(src, []), "-I", INCLUDE, "-I", CSRC, "-c",
+                     os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
+    with concurrent.futures.ThreadPoolExecutor(max_workers=4) as pool:   # memory: a compiler is about 1 GB
+        for done in [pool.submit(_run, cmd, verbose) for cmd in jobs]:
+            done.result()
     lib = SANITIZED_LIB if sanitize else LIB
     tmp = lib + ".tmp"
     if sanitize:   # g++ links the sanitizer runtimes its host objects were built for

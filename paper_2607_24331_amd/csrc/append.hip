@@ -29,8 +29,8 @@ constexpr int kTileTok = 64;
 constexpr int kTileCol = 64;
 constexpr int kTileK = 16;
 
-// Portable VALU kernel (fp32 latents, and bf16 when the MFMA path does not
-// apply): 64 tokens x 64 columns per 256-thread block, 4x4 outputs a thread.
+// Portable VALU kernel (where m is a multiple of neither 64, bf16, nor 16,
+// fp32): 64 tokens x 64 columns per 256-thread block, 4x4 outputs a thread.
 template <typename T>
 __global__ __launch_bounds__(256) void append_valu(const T* __restrict__ x, const T* __restrict__ Lk,
                                                    const T* __restrict__ Lv,
