@@ -433,9 +433,14 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context,
     // over the compute units where that leaves one a sequence and none longer
     // than the split kernel's page list.  Fixed splits are sized by
     // max_context: 64 sequences of 1024 to 8192 tokens leave a third of the
-    // compute units without work (split kernel 370 us, balanced 292; the
-    // record's load before all others costs equal lengths 0.7 us of 88); one
-    // sequence is cut evenly as it is.
+    // compute units without work (split kernel 370 us, balanced 292).  The
+    // line does not lie at a batch: the host does not know the lengths, and
+    // whole calls on a 32/8-head layer over lengths of an eighth to the whole
+    // of 131072 / batch tokens go 74.6 -> 69.6 us at 2 sequences, 70.0 -> 61.1
+    // at 4, 80.3 -> 70.1 at 16, 90.3 -> 80.1 at 64, while equal lengths pay
+    // for the record's load before all others: 88.3 -> 89.2 at 2, 88.1 ->
+    // 89.4 at 4, 95.7 -> 96.8 at 16, 102.2 -> 102.8 at 64.  One sequence is
+    // cut evenly as it is.
     if (!plain && p.split_tokens == 0 && batch >= 2 && batch <= kSchedMaxBatch && units <= kSchedMaxUnits &&
         (p.dh == 64 || p.dh == 128)) {
       const int64_t npm = (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS;
