@@ -228,13 +228,14 @@ __device__ __forceinline__ void read_rows(short8_t (&f)[2 * NS], uint32_t p0, ui
 // The end of a tile: the two waves of a position exchange halves of their
 // sums through LDS (kh = 0 keeps the upper row fragments, kh = 1 the lower),
 // add them and write the tile and its mirror.  A diagonal tile writes its
-// upper triangle and the mirror of it.  fix(i, j, t) has the last word on an
-// element's value.
-template <int NS, typename Fix>
-__device__ __forceinline__ void gram_write(floatx4 (&acc)[2 * NS][2 * NS], unsigned char* smem,
+// upper triangle and the mirror of it.  Returns whether this thread wrote an
+// element that is not finite.
+template <int NS>
+__device__ __forceinline__ bool gram_write(floatx4 (&acc)[2 * NS][2 * NS], unsigned char* smem,
                                            float* __restrict__ G, int cols, int i0, int j0, int wi,
-                                           int wj, int kh, int pos, int lane, Fix fix) {
+                                           int wj, int kh, int pos, int lane) {
   constexpr int F = 2 * NS;
+  bool odd = false;
   const int lr = lane & 15, lq = lane >> 4;
   floatx4* ex = reinterpret_cast<floatx4*>(smem) + lane;         // [8][NS * F][64]
   const bool diag = i0 == j0;
@@ -254,7 +255,7 @@ __device__ __forceinline__ void gram_write(floatx4 (&acc)[2 * NS][2 * NS], unsig
         floatx4 t = acc[x0 + x][y] + ex[((slot * NS + x) * F + y) * 64];
         if (i >= cols || j >= cols) continue;                    // cols is a multiple of 8
 #pragma unroll
-        for (int v = 0; v < 4; ++v) t[v] = fix(i + v, j, t[v]);
+        for (int v = 0; v < 4; ++v) odd |= !(fabsf(t[v]) < INFINITY);
         if (!diag) {
           *reinterpret_cast<floatx4*>(G + int64_t(j) * cols + i) = t;
 #pragma unroll
@@ -276,6 +277,7 @@ __device__ __forceinline__ void gram_write(floatx4 (&acc)[2 * NS][2 * NS], unsig
   __syncthreads();
   if (kh == 0) finish(0, 4 + pos);
   else finish(NS, pos);
+  return odd;
 }
 
 // bf16 samples, no centring: the samples are the operands, every product is
@@ -373,8 +375,7 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_bf16(const bf16* __restr
     __syncthreads();
     products(smem);
   }
-  gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane,
-                 [](int, int, float t) { return t; });
+  gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane);
 }
 
 // Any samples: d = a - mu in fp32, taken as the exact sum of three bf16 parts
@@ -401,6 +402,13 @@ __device__ __forceinline__ void split_pair(float d0, float d1, uint32_t& h, uint
   m = uint32_t(__builtin_bit_cast(uint16_t, m0)) | (uint32_t(__builtin_bit_cast(uint16_t, m1)) << 16);
   const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xFFFF0000u);
   l = (__float_as_uint(s0) >> 16) | (__float_as_uint(s1) & 0xFFFF0000u);
+}
+
+// The class of d as bf16: 0, +-1, +-inf or NaN.
+__device__ __forceinline__ uint32_t class_of(float d) {
+  const uint32_t u = __float_as_uint(d), m = u & 0x7FFFFFFFu;
+  if (m > 0x7F800000u) return 0x7FC0u;
+  return (u >> 16 & 0x8000u) | (m == 0 ? 0u : m < 0x7F800000u ? 0x3F80u : 0x7F80u);
 }
 
 template <typename T, int NS>
@@ -447,31 +455,37 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
 #pragma unroll
       for (int k = 0; k < NQ; ++k) raw[q][k] = *reinterpret_cast<const u32x4*>(base + goff[q] + 16 * k);
   };
-  auto convert = [&](int st, unsigned char* buf) {
+  // the loaded values of chunk q, zero past the last row: put(k, two of them)
+  auto values = [&](int st, int q, auto put) {
     const bool live = int64_t(st) * 32 + crow < rows;
+    const floatx4 m0 = *reinterpret_cast<const floatx4*>(smu + moff[q]);
+    const floatx4 m1 = *reinterpret_cast<const floatx4*>(smu + moff[q] + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float d0, d1;
+      if constexpr (NQ == 2) {
+        d0 = __uint_as_float(raw[q][k >> 1][2 * (k & 1)]);
+        d1 = __uint_as_float(raw[q][k >> 1][2 * (k & 1) + 1]);
+      } else {
+        d0 = __uint_as_float(raw[q][0][k] << 16);
+        d1 = __uint_as_float(raw[q][0][k] & 0xFFFF0000u);
+      }
+      d0 -= k < 2 ? m0[2 * k] : m1[2 * k - 4];
+      d1 -= k < 2 ? m0[2 * k + 1] : m1[2 * k - 3];
+      put(k, live ? d0 : 0.f, live ? d1 : 0.f);
+    }
+  };
+  auto convert = [&](int st, unsigned char* buf) {
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
-      const floatx4 m0 = *reinterpret_cast<const floatx4*>(smu + moff[q]);
-      const floatx4 m1 = *reinterpret_cast<const floatx4*>(smu + moff[q] + 4);
       u32x4 h, m, l;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float d0, d1;
-        if constexpr (NQ == 2) {
-          d0 = __uint_as_float(raw[q][k >> 1][2 * (k & 1)]);
-          d1 = __uint_as_float(raw[q][k >> 1][2 * (k & 1) + 1]);
-        } else {
-          d0 = __uint_as_float(raw[q][0][k] << 16);
-          d1 = __uint_as_float(raw[q][0][k] & 0xFFFF0000u);
-        }
-        d0 -= k < 2 ? m0[2 * k] : m1[2 * k - 4];
-        d1 -= k < 2 ? m0[2 * k + 1] : m1[2 * k - 3];
+      values(st, q, [&](int k, float d0, float d1) {
         uint32_t ph, pm, pl;
-        split_pair(live ? d0 : 0.f, live ? d1 : 0.f, ph, pm, pl);
+        split_pair(d0, d1, ph, pm, pl);
         h[k] = ph;
         m[k] = pm;
         l[k] = pl;
-      }
+      });
       *reinterpret_cast<u32x4*>(buf + soff[q]) = h;
       *reinterpret_cast<u32x4*>(buf + PL + soff[q]) = m;
       *reinterpret_cast<u32x4*>(buf + 2 * PL + soff[q]) = l;
@@ -553,17 +567,56 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
       __syncthreads();
     }
   }
-  // infinities do not survive the split (inf has NaN for a rest, and inf times
-  // a part that is 0 is NaN): an element that is not finite is summed again
-  // from the samples themselves
-  gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane, [&](int i, int j, float t) {
-    if (fabsf(t) < INFINITY) return t;
-    const float mi = smu[i - i0], mj = smu[64 * NS + j - j0];
-    float f = 0.f;
-    for (int64_t r = 0; r < rows; ++r)
-      f = fmaf(to_f32(A[r * cols + i]) - mi, to_f32(A[r * cols + j]) - mj, f);
-    return f;
-  });
+  if (!__syncthreads_or(gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane))) return;
+
+  // Infinities do not survive the split (inf has NaN for a rest, and inf times
+  // a part that is 0 is NaN).  A tile that holds an element that is not finite
+  // walks its samples once more and takes each as its class: 0, +-1 for a
+  // finite value, +-inf, NaN.  Sums of products of classes are infinite or NaN
+  // where those of the values are, and those elements are written again;
+  // where they are finite the samples are too, and what was written is a sum
+  // that left fp32's range.  One product a term: whatever the samples hold,
+  // less than the walk above took.
+#pragma unroll
+  for (int x = 0; x < F; ++x)
+#pragma unroll
+    for (int y = 0; y < F; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int st = 0; st < nst; ++st) {
+    __syncthreads();                                             // the stage before has been read
+    load(st);
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      u32x4 c;
+      values(st, q, [&](int k, float d0, float d1) { c[k] = class_of(d0) | class_of(d1) << 16; });
+      *reinterpret_cast<u32x4*>(smem + soff[q]) = c;
+    }
+    __syncthreads();
+    if (kh == 0) {
+      short8_t a[F];
+#pragma unroll
+      for (int x = 0; x < F; ++x) a[x] = read_frag(smem + oi[x & 1] + (x >> 1) * 4096);
+#pragma unroll
+      for (int y = 0; y < F; ++y) {
+        const short8_t b = read_frag(smem + oj[y & 1] + (y >> 1) * 4096);
+#pragma unroll
+        for (int x = 0; x < F; ++x) acc[x][y] = mfma_bf16(a[x], b, acc[x][y]);
+      }
+    }
+  }
+  if (kh != 0) return;
+#pragma unroll
+  for (int x = 0; x < F; ++x)
+#pragma unroll
+    for (int y = 0; y < F; ++y) {
+      const int i = i0 + 64 * (x >> 1) + 32 * wi + 16 * (x & 1) + 4 * lq;
+      const int j = j0 + 64 * (y >> 1) + 32 * wj + 16 * (y & 1) + li;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (i < cols && j < cols && (i0 != j0 || i + v <= j) && !(fabsf(acc[x][y][v]) < INFINITY)) {
+          G[int64_t(j) * cols + i + v] = acc[x][y][v];
+          G[int64_t(i + v) * cols + j] = acc[x][y][v];
+        }
+    }
 }
 
 // F[i][j] = F[j][i] = ||G_ij||_F^2 (i <= j), one work-group a block, fixed-order

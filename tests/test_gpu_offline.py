@@ -95,6 +95,56 @@ def test_gram_of_infinities_and_nans(dtype):
     assert np.array_equal(got, ref, equal_nan=True)
 
 
+# samples that are not finite over 64-, 128- and 192-column tiles and many row
+# stages: a whole row of NaN, a row of infinities of both signs, and single ones
+# in columns that meet zeros.  Small integers, so that every finite element is
+# exact; centred, a column with such a sample has a mean that is not finite, and
+# its whole row and column of G are NaN.  The call takes at most as long again
+# as with finite samples, whatever they hold (a factor of 3 and 2 ms here, for
+# the clock).
+@pytest.mark.parametrize("cols", [136, 2816, 4096])
+@pytest.mark.parametrize("dtype, center", [("f32", False), ("f32", True), ("bf16", True)])
+@pytest.mark.parametrize("kind", ["nan_row", "inf_row", "single"])
+def test_gram_not_finite_at_length(cols, dtype, center, kind):
+    from paper_2607_24331_amd import gram
+    rows = 4099
+    g = np.random.default_rng(cols)
+    A = g.integers(-2, 3, (rows, cols)).astype(np.float32)
+    bad = np.arange(cols)
+    finite = A.copy()
+    if kind == "nan_row":
+        A[rows - 1] = np.nan
+    elif kind == "inf_row":
+        A[17] = np.where(np.arange(cols) % 3 == 0, -np.inf, np.inf)
+    else:
+        bad = np.array([3, 70, 71, cols - 1])
+        A[[5, 4000, 4000, 9], bad] = [np.inf, np.nan, -np.inf, -np.inf]
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    At, Ft = torch.from_numpy(A).cuda().to(tdt), torch.from_numpy(finite).cuda().to(tdt)
+
+    def timed(X):
+        best, G = float("inf"), gram(X, center=center)
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            G = gram(X, center=center)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return G.cpu().numpy(), best
+    got, t_bad = timed(At)
+    good, t_good = timed(Ft)
+    assert t_bad <= 3 * t_good + 2.0, (t_bad, t_good)
+    if center:                                # the finite columns' means do not change
+        ref = good
+        ref[bad, :] = np.nan
+        ref[:, bad] = np.nan
+    else:
+        with np.errstate(invalid="ignore"):
+            ref = A.astype(np.float64).T @ A.astype(np.float64)
+    assert np.array_equal(got, ref.astype(np.float32), equal_nan=True)
+
+
 def test_gram_is_bitwise_reproducible():
     from paper_2607_24331_amd import gram
     A = torch.randn(777, 200, device="cuda")
