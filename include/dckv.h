@@ -357,7 +357,11 @@ int dckv_dense_decode(int32_t num_q_heads, int32_t num_kv_heads, int32_t head_di
  *              when that is 0), 256-byte aligned
  * Sums are fp32 in a fixed order: bitwise reproducible.  Products are those
  * of bf16 samples, exact in fp32, or of fp32 values (fp32 or centred samples)
- * taken as three bf16 parts each, to below 2^-22 of a product.  Errors: DCKV_EINVAL (shape, null pointer), DCKV_EDTYPE,
+ * taken as three bf16 parts each: exact for at most 32 rows, to below 2^-22 of
+ * a product (2^-24 and less in the mean) for more, where the sums' own
+ * roundings are larger.  A sample that is not finite makes its elements of G
+ * infinite or NaN as products and sums of the values would, and the call
+ * take at most twice as long.  Errors: DCKV_EINVAL (shape, null pointer), DCKV_EDTYPE,
  * DCKV_EALIGN, DCKV_EWORKSPACE, DCKV_EHIP; nothing is launched on error. */
 int dckv_gram_workspace_bytes(int64_t rows, int32_t cols, int32_t center, size_t* bytes);
 int dckv_gram(const void* A, int32_t dtype, int64_t rows, int32_t cols, int32_t center, float* G,

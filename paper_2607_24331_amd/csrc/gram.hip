@@ -390,6 +390,12 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_bf16(const bf16* __restr
 // LDS buffers beside the products of the current one.  mu: null (no
 // centring), the means (nblk 0), or nblk row blocks' column sums, of which
 // every work-group takes the means of its own columns.
+// FEW, for at most 32 rows (one stage): all nine products, kh = 0 taking hi hi
+// alone (at most 16 significant bits a product) and kh = 1 the other eight, so
+// that the one rounding of a large sum is the last addition's, as in a single
+// fp32 product.  With few terms the three products left out would show: 2-norm
+// error of one row 4.0e-8 with six products, 2.5e-8 on the fp32 matrix
+// instruction and here; of 8 rows 4.7e-8 / 5.3e-8 / 2.8e-8.
 // Bound by the matrix pipe (six products) with the splitting beside it: 2048 x
 // 4096 fp32 samples, centred, 205 us against 395 us on the fp32 matrix
 // instruction, error against float64 4.9e-7 against 7.5e-7 (2-norm; bf16
@@ -411,7 +417,7 @@ __device__ __forceinline__ uint32_t class_of(float d) {
   return (u >> 16 & 0x8000u) | (m == 0 ? 0u : m < 0x7F800000u ? 0x3F80u : 0x7F80u);
 }
 
-template <typename T, int NS>
+template <typename T, int NS, bool FEW = false>
 __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restrict__ A, int64_t rows,
                                                              int cols, const float* __restrict__ mu,
                                                              int nblk, float* __restrict__ G, int nt,
@@ -542,29 +548,52 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
     }
     if (NS == 3) __builtin_amdgcn_sched_barrier(0);
   };
+  // the products of part p of one operand and part q of the other
+  auto part_part = [&](int p, int q) {
+    short8_t a[F];
+#pragma unroll
+    for (int x = 0; x < F; ++x) a[x] = read_frag(smem + p * PL + oi[x & 1] + (x >> 1) * 4096);
+#pragma unroll
+    for (int y = 0; y < F; ++y) {
+      const short8_t b = read_frag(smem + q * PL + oj[y & 1] + (y >> 1) * 4096);
+#pragma unroll
+      for (int x = 0; x < F; ++x) acc[x][y] = mfma_bf16(a[x], b, acc[x][y]);
+    }
+  };
   load(0);
   __syncthreads();                                               // the means
   convert(0, smem);
   __syncthreads();
-  // the two waves of a SIMD take the stage in opposite order, so one splits
-  // while the other multiplies
-  if (NS < 3 || kh == 0) load(1);
-  if (kh == 0) {
-    for (int st = 0; st < nst; ++st) {
-      convert(st + 1, smem + ((st + 1) & 1) * BUF);
-      load(st + 2);
-      if (NS == 3) __builtin_amdgcn_sched_barrier(0);
-      cross(smem + (st & 1) * BUF, std::integral_constant<int, PL>{}, std::true_type{});
-      __syncthreads();
+  if constexpr (FEW) {
+    if (kh == 0) {
+      part_part(0, 0);
+    } else {
+#pragma unroll
+      for (int s = 4; s >= 1; --s)                               // small products first
+#pragma unroll
+        for (int p = max(0, s - 2); p <= min(2, s); ++p) part_part(p, s - p);
     }
   } else {
-    for (int st = 0; st < nst; ++st) {
-      cross(smem + (st & 1) * BUF, std::integral_constant<int, 2 * PL>{}, std::false_type{});
-      if (NS == 3) load(st + 1);             // later than need be: registers
-      mid_mid(smem + (st & 1) * BUF);
-      convert(st + 1, smem + ((st + 1) & 1) * BUF);
-      if (NS < 3) load(st + 2);
-      __syncthreads();
+    // the two waves of a SIMD take the stage in opposite order, so one splits
+    // while the other multiplies
+    if (NS < 3 || kh == 0) load(1);
+    if (kh == 0) {
+      for (int st = 0; st < nst; ++st) {
+        convert(st + 1, smem + ((st + 1) & 1) * BUF);
+        load(st + 2);
+        if (NS == 3) __builtin_amdgcn_sched_barrier(0);
+        cross(smem + (st & 1) * BUF, std::integral_constant<int, PL>{}, std::true_type{});
+        __syncthreads();
+      }
+    } else {
+      for (int st = 0; st < nst; ++st) {
+        cross(smem + (st & 1) * BUF, std::integral_constant<int, 2 * PL>{}, std::false_type{});
+        if (NS == 3) load(st + 1);             // later than need be: registers
+        mid_mid(smem + (st & 1) * BUF);
+        convert(st + 1, smem + ((st + 1) & 1) * BUF);
+        if (NS < 3) load(st + 2);
+        __syncthreads();
+      }
     }
   }
   if (!__syncthreads_or(gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane))) return;
@@ -702,7 +731,7 @@ hipError_t launch_gram_kernel(K kern, size_t lds, int n_tiles, hipStream_t strea
   return hipGetLastError();
 }
 
-template <int NS>
+template <int NS, bool FEW = false>
 hipError_t launch_tiles(const void* A, int32_t dtype, int64_t rows, int32_t cols, const float* mu,
                         int nblk, float* G, hipStream_t stream) {
   const int nt = (cols + 64 * NS - 1) / (64 * NS), n_tiles = nt * (nt + 1) / 2;
@@ -714,9 +743,9 @@ hipError_t launch_tiles(const void* A, int32_t dtype, int64_t rows, int32_t cols
     return launch_gram_kernel(gram_bf16<NS>, lds_bf16, n_tiles, stream, static_cast<const bf16*>(A),
                               rows, int(cols), G, nt, n_tiles);
   if (dtype == DCKV_BF16)
-    return launch_gram_kernel(gram_split<bf16, NS>, lds_split, n_tiles, stream,
+    return launch_gram_kernel(gram_split<bf16, NS, FEW>, lds_split, n_tiles, stream,
                               static_cast<const bf16*>(A), rows, int(cols), mu, nblk, G, nt, n_tiles);
-  return launch_gram_kernel(gram_split<float, NS>, lds_split, n_tiles, stream,
+  return launch_gram_kernel(gram_split<float, NS, FEW>, lds_split, n_tiles, stream,
                             static_cast<const float*>(A), rows, int(cols), mu, nblk, G, nt, n_tiles);
 }
 
@@ -755,6 +784,10 @@ hipError_t launch_gram(const void* A, int32_t dtype, int64_t rows, int32_t cols,
       sums = 0;
     }
   }
+  // one stage of rows: every product (precision; bf16 samples that are not
+  // centred are exact as they are)
+  if (rows <= 32 && (mu || dtype == DCKV_F32))
+    return launch_tiles<1, true>(A, dtype, rows, cols, mu, sums, G, stream);
   // Tile size: the one whose most loaded compute unit has the least work
   // (one work-group a compute unit), a tile of NS slabs a side costing NS^2
   // products and NS of staging

@@ -145,6 +145,39 @@ def test_gram_not_finite_at_length(cols, dtype, center, kind):
     assert np.array_equal(got, ref.astype(np.float32), equal_nan=True)
 
 
+# at most 32 samples: every product of parts is summed, so G is no further off
+# float64 (2-norm) than fp32 products added in sample order (for one sample the
+# product rounded once: half a unit of the last place for each element, and a
+# sixty-fourth more for the parts' own sum, whose roundings are that small)
+@pytest.mark.parametrize("rows", [1, 2, 3, 5, 8, 31, 32])
+@pytest.mark.parametrize("dtype, center", [("f32", False), ("f32", True), ("bf16", True)])
+def test_gram_of_few_rows_is_no_further_off_than_fp32(rows, dtype, center):
+    from paper_2607_24331_amd import gram
+    g = np.random.default_rng(rows)
+    A = (g.standard_normal((rows, 200)) + 0.25 * g.standard_normal(200)[None, :]).astype(np.float32)
+    At = torch.from_numpy(A).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    A = At.float().cpu().numpy()
+    D = A - (A.sum(axis=0, dtype=np.float32) / np.float32(rows))[None, :] if center else A
+    seq = np.zeros((200, 200), np.float32)
+    for r in range(rows):
+        seq += np.outer(D[r], D[r])
+    got = gram(At, center=center).double().cpu().numpy()
+    A64 = A.astype(np.float64)
+    ref = ocal.gram(oc.centered(A64) if center else A64)
+    assert np.linalg.norm(got - ref) <= 1.02 * np.linalg.norm(seq - ref)
+    if rows == 1 and not center:
+        assert np.all(np.abs(got - ref) <= (1 + 2.0 ** -6) * 2.0 ** -24 * np.abs(ref))
+
+
+def test_gram_of_few_rows_not_finite():
+    from paper_2607_24331_amd import gram
+    A = np.random.default_rng(5).integers(-4, 5, (20, 136)).astype(np.float32)
+    A[7, 3], A[9, 70] = -np.inf, np.nan
+    with np.errstate(invalid="ignore"):
+        ref = np.stack([(A[:, i:i + 1] * A).sum(axis=0) for i in range(A.shape[1])])
+    assert np.array_equal(gram(torch.from_numpy(A).cuda(), center=False).cpu().numpy(), ref, equal_nan=True)
+
+
 def test_gram_is_bitwise_reproducible():
     from paper_2607_24331_amd import gram
     A = torch.randn(777, 200, device="cuda")
