@@ -179,7 +179,10 @@ int dckv_plan_info(const dckv_plan* plan, dckv_plan_geometry* geo, int32_t* koff
                    int32_t* pos_in_group, int32_t* qoff, int64_t* roff);
 
 /* Bytes of device workspace dckv_decode needs for `batch` sequences of at
- * most `max_context` tokens.  Makes no HIP call. */
+ * most `max_context` tokens.  A buffer of this size also serves every call of
+ * the plan with fewer sequences or a shorter max_context, except between two
+ * calls on the two-pass kernels (dckv_launch_info below), whose sizes are each
+ * call's own.  Makes no HIP call. */
 int dckv_decode_workspace_bytes(const dckv_plan* plan, int32_t batch, int32_t max_context,
                                 size_t* bytes);
 
@@ -255,8 +258,11 @@ int dckv_decode(const dckv_plan* plan, const float* q, int32_t batch, const void
  * arguments, validation and bitwise results as dckv_decode, without the
  * workspace: the scratch lives in a fixed device array of
  * DCKV_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until
- * the process ends.  A call whose dckv_decode_workspace_bytes exceeds that
- * size returns DCKV_EWORKSPACE and enqueues nothing.  The call itself never
+ * the process ends.  A call whose own scratch (folded queries, partials of its
+ * splits, merged rows; at most dckv_decode_workspace_bytes) exceeds that size
+ * returns DCKV_EWORKSPACE and enqueues nothing; the records by which the
+ * library cuts a batch by its actual lengths (at most 10 KB) have room of
+ * their own beside it.  The call itself never
  * calls hipMalloc or hipFree; the first call on a device looks the array's
  * address up once (hipGetSymbolAddress).  Every call on one GPU shares that
  * GPU's array: calls that may overlap on one GPU (different streams, several

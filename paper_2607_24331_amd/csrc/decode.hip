@@ -362,6 +362,24 @@ static DecodeShape pass_shape(const dckv_plan& p, int32_t batch, int32_t max_con
   return s;
 }
 
+// Workspace of the single-pass and the portable kernels whose splits leave
+// `rows` rows of partials.
+static void lay_out(const dckv_plan& p, DecodeShape& s, size_t rows) {
+  const size_t nh = s.mfma ? 16 * size_t(p.mfma.nt) : 1;
+  s.off_qt = 0;
+  s.off_ml = s.mfma   // hi/lo query blocks of 2 KB per (sequence, slice, chunk)
+                 ? align_up(size_t(s.batch) * p.mfma.n_slices * p.mfma.max_pairs * 2048, 256)
+                 : align_up(size_t(s.batch) * p.Q * p.qlen * sizeof(float), 256);
+  s.off_acc = s.off_ml + align_up(rows * 2 * nh * sizeof(float), 256);
+  s.off_opart = s.off_acc + align_up(rows * nh * size_t(p.rv) * sizeof(float), 256);
+  s.bytes = s.off_opart;
+  if (s.mfma) s.bytes += align_up(size_t(s.batch) * p.Q * p.Hq * p.rv * sizeof(float), 256);
+}
+
+static size_t sched_bytes(int64_t units, int32_t batch) {
+  return align_up(size_t(units) * sizeof(SchedUnit) + size_t(batch) * sizeof(SchedSeq), 256);
+}
+
 DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context, bool plain) {
   // The two-pass kernels when asked for, when the single-pass kernel does not
   // apply, or when it would cut the rows into several slices (a value rank
@@ -413,20 +431,12 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context,
   if (s.mfma && L > mfma_max_split_tokens()) s.mfma = false;   // an explicit split beyond the cap
   s.split_tokens = int32_t(L);
   s.n_split = max_context > 0 ? int32_t((max_context + L - 1) / L) : 1;
-  s.off_qt = 0;
-  s.off_ml = align_up(size_t(batch) * p.Q * p.qlen * sizeof(float), 256);
-  if (s.mfma)   // the MFMA path keeps hi/lo query blocks of 2 KB per (sequence, slice, chunk)
-    s.off_ml = align_up(size_t(batch) * p.mfma.n_slices * p.mfma.max_pairs * 2048, 256);
+  lay_out(p, s, size_t(batch) * s.n_split * (s.mfma ? p.mfma.n_slices : p.Q * p.Hq));
   if (s.mfma) {
     const int64_t units = int64_t(batch) * s.n_split;
     s.n_units = int32_t((units + 7) / 8 * 8);
     s.merge_ranks = mfma_merge_ranks(p, batch);
     s.n_rchunks = (p.rv + s.merge_ranks - 1) / s.merge_ranks;
-    const size_t nh = 16 * size_t(p.mfma.nt);
-    const size_t rows = size_t(batch) * p.mfma.n_slices * s.n_split;
-    s.off_acc = s.off_ml + align_up(rows * 2 * nh * sizeof(float), 256);
-    s.off_opart = s.off_acc + align_up(rows * nh * size_t(p.rv) * sizeof(float), 256);
-    s.bytes = s.off_opart + align_up(size_t(batch) * p.Q * p.Hq * p.rv * sizeof(float), 256);
     // Balanced splits: several sequences, no split size asked for, and a head
     // size whose fold kernel cuts them.  Never more splits than the fixed cut
     // has (their partials share its workspace), and a whole number of rounds
@@ -452,16 +462,34 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context,
       s.n_sched = int32_t(U);
       s.n_units = int32_t((U + 7) / 8 * 8);
       s.off_sched = s.bytes;
-      s.sched_bytes = align_up(size_t(U) * sizeof(SchedUnit) + size_t(batch) * sizeof(SchedSeq), 256);
+      s.sched_bytes = sched_bytes(U, batch);
       s.bytes += s.sched_bytes;
     }
-  } else {
-    const size_t rows = size_t(batch) * p.Q * p.Hq * s.n_split;
-    s.off_acc = s.off_ml + align_up(rows * 2 * sizeof(float), 256);
-    s.off_opart = s.off_acc + align_up(rows * p.rv * sizeof(float), 256);
-    s.bytes = s.off_opart;
   }
   return s;
+}
+
+// A buffer of this size serves every call of at most that many sequences and
+// tokens.  Where the library chooses the split size, a shorter context may
+// leave more splits (longer splits come in whole pages), so the size is not
+// the call's own but that of a bound on the rows of partials: splits that were
+// lengthened to make about kTargetWorkgroups of them are at most that many and
+// one more a row of the batch, and never more than a page each; those at the
+// longest split length grow with the context.
+size_t decode_workspace_bytes(const dckv_plan& p, int32_t batch, int32_t max_context) {
+  const DecodeShape s = decode_shape(p, batch, max_context);
+  if (p.split_tokens > 0 || (s.pass && (p.decode_passes == 2 || !p.mfma_ok))) return s.bytes;
+  DecodeShape t{};
+  t.batch = batch;
+  t.mfma = p.mfma_ok;
+  const int64_t per_seq = p.mfma_ok ? p.mfma.n_slices : int64_t(p.Q) * p.Hq;
+  const int64_t longest = (p.mfma_ok ? mfma_max_split_tokens() : kValuSplitTokens) / DCKV_PAGE_TOKENS;
+  const int64_t npm = std::max<int64_t>(1, (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS);
+  const int64_t rows = std::max(batch * per_seq * ((npm + longest - 1) / longest),
+                                std::min(kTargetWorkgroups + batch * per_seq, batch * per_seq * npm));
+  lay_out(p, t, size_t(rows));
+  if (t.mfma) t.bytes += sched_bytes(kSchedMaxUnits, std::min(batch, kSchedMaxBatch));
+  return std::max(s.bytes, t.bytes);
 }
 
 hipError_t launch_decode(const dckv_plan& p, const DecodeShape& shape, const float* q,

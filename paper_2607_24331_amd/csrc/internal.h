@@ -239,6 +239,7 @@ hipError_t launch_decode_rope(const dckv_plan& p, const DecodeShape& sh, const f
 // Defined in the kernel sources.
 // plain: fixed splits and one value slice (the rotary decode's)
 DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context, bool plain = false);
+size_t decode_workspace_bytes(const dckv_plan& p, int32_t batch, int32_t max_context);
 DenseShape dense_shape(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t batch,
                        int32_t max_context, int32_t split_tokens);
 hipError_t launch_dense_decode(const DenseShape& sh, const float* q, const void* pool,

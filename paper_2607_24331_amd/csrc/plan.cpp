@@ -504,7 +504,7 @@ int dckv_decode_workspace_bytes(const dckv_plan* p, int32_t batch, int32_t max_c
   if (batch < 0 || max_context < 0)
     return fail(DCKV_EINVAL, "decode_workspace_bytes: negative batch %d or max_context %d", batch,
                 max_context);
-  *bytes = dckv::decode_shape(*p, batch, max_context).bytes;
+  *bytes = dckv::decode_workspace_bytes(*p, batch, max_context);
   return DCKV_OK;
 }
 

@@ -118,6 +118,37 @@ def test_workspace_bytes_grows_with_work():
         assert p.workspace_bytes(4, 0) > 0
 
 
+# what a call needs is read from the message that refuses it a workspace of no
+# bytes: nothing is launched, with or without a GPU
+def _needed(lib, plan, batch, max_context):
+    A = 1 << 20
+    st = lib.dckv_decode(plan.handle, A, batch, A, 4, A, 1 << 20, A, max_context, A, A, A, A, 0, None)
+    assert st == capi.DCKV_EWORKSPACE
+    return int(lib.dckv_last_error().decode().split(", ")[-1].split()[0])
+
+
+# a workspace sized for a batch and a longest context serves every smaller
+# batch and shorter context: the portable kernels, the single-pass kernel with
+# and without value halves, one and several row slices, splits given
+@pytest.mark.parametrize("dtype, heads, d, rv, queries, split", [
+    ("f32", 8, 64, 128, 1, 0), ("f32", 4, 64, 200, 8, 0), ("f32", 8, 64, 128, 1, 256), ("bf16", 12, 12, 100, 1, 0),
+    ("bf16", 32, 128, 2048, 1, 0), ("bf16", 32, 128, 768, 1, 0), ("bf16", 32, 64, 2048, 2, 0),
+    ("bf16", 8, 64, 144, 8, 0), ("bf16", 32, 128, 1536, 1, 128)])
+def test_workspace_serves_every_smaller_call(lib, dtype, heads, d, rv, queries, split):
+    from paper_2607_24331_amd import Plan
+    p = Plan(4096, heads, heads, d, [i % 3 for i in range(heads)], [20, 30, 40], rv, dtype, split,
+             queries_per_seq=queries, **({"decode_passes": 1} if dtype == "bf16" else {}))
+    contexts = sorted({0, 1, 64, 65, *(64 * n + 1 for n in (2, 5, 16, 31, 32, 33, 63, 64, 100, 127, 128, 129,
+                                                            255, 256, 511, 777, 1025, 2047, 4096, 9000))})
+    for top in (1, 2, 3, 8, 33, 64, 200, 256, 257, 300):
+        most = 0
+        for c in contexts:
+            most = max([most] + [_needed(lib, p, b, n) for b in {1, top // 2 or 1, max(1, top - 1), top}
+                                 for n in (c, max(0, c - 1), c // 2)])
+            assert p.workspace_bytes(top, c) >= most, (top, c)
+            assert top == 1 or p.workspace_bytes(top, c) >= p.workspace_bytes(top - 1, c)
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="raw fake pointers are only passed on a host without a GPU")
 def test_call_validation_never_launches(lib):
     wl = make_workload("tiny_mha_f32")
