@@ -650,7 +650,7 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
 
 // F[i][j] = F[j][i] = ||G_ij||_F^2 (i <= j), one work-group a block, fixed-order
 // sums; F is written into S's memory and turned into S by head_sim_finish.
-// VEC (d a multiple of 4): 32 threads a row of the block, 16-byte loads, eight
+// VEC (d a multiple of 4, G 16-byte aligned): 32 threads a row of the block, 16-byte loads, eight
 // rows in flight; else one value at a time.
 template <bool VEC>
 __global__ __launch_bounds__(256) void head_sim_blocks(const float* __restrict__ G, int h, int d,
@@ -808,7 +808,9 @@ hipError_t launch_gram(const void* A, int32_t dtype, int64_t rows, int32_t cols,
 
 hipError_t launch_head_similarity(const float* G, int32_t h, int32_t d, float* S,
                                   hipStream_t stream) {
-  if (d % 4 == 0)
+  // 16-byte loads where every row of a block starts on 16 bytes; G itself need
+  // only be aligned to its elements
+  if (d % 4 == 0 && aligned(G, 16))
     hipLaunchKernelGGL(head_sim_blocks<true>, dim3(h, h), dim3(256), 0, stream, G, h, d, S);
   else
     hipLaunchKernelGGL(head_sim_blocks<false>, dim3(h, h), dim3(256), 0, stream, G, h, d, S);

@@ -233,6 +233,26 @@ def test_head_similarity_full_size_sampled():
     assert np.all(np.abs(G.double().cpu().numpy()[rows] - ref_rows) <= bound)
 
 
+# every start of G that its 4-byte alignment allows, with head sizes that are and
+# are not a multiple of 4; float64 sums of the same G, bound of d^2 fp32 additions
+@pytest.mark.parametrize("h, d", [(3, 64), (5, 36), (4, 30)])
+@pytest.mark.parametrize("first", [0, 1, 2, 3])
+def test_head_similarity_of_any_alignment(h, d, first):
+    from paper_2607_24331_amd import head_similarity
+    n = h * d
+    g = np.random.default_rng(n + first)
+    X = g.standard_normal((2 * n, n))
+    G = (X.T @ X).astype(np.float32)
+    buf = torch.zeros(n * n + 4, device="cuda")
+    Gt = buf[first:first + n * n].view(n, n)
+    Gt.copy_(torch.from_numpy(G))
+    assert Gt.data_ptr() % 16 == 4 * first
+    got = head_similarity(Gt, h, d).double().cpu().numpy()
+    F = (G.astype(np.float64).reshape(h, d, h, d) ** 2).sum(axis=(1, 3))
+    ref = F / np.sqrt(np.outer(np.diag(F), np.diag(F)))
+    assert np.all(np.abs(got - ref) <= 2 * (d * d + 8) * U32 * np.abs(ref))
+
+
 def test_compress_keys_matches_oracle():
     from paper_2607_24331_amd import cluster_merges
     from paper_2607_24331_amd.offline import compress_keys, key_similarity
