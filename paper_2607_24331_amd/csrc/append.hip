@@ -383,18 +383,17 @@ hipError_t launch_append_mfma(const dckv_plan& p, const void* x, int32_t n_tok, 
 
 // Few tokens (a decode step's, at most 16 NT): bound by reading L once.  One
 // work-group a 16-column tile of L for all tokens, its eight waves splitting
-// k; a wave keeps sixteen 16-byte loads of L (512 k of its 16 rows) in flight,
-// which over the work-group is a whole 128 KB tile at m = 4096, and takes the
-// token operands (read by every work-group, so from L2) all (NT = 1) or half
-// of them (NT = 2) ahead.  The waves' sums are added in wave order through
-// LDS.  8 tokens, m = 4096, 4096 columns: 11 us (3.0 TB/s; 19 us on 128 x 64
-// tiles).
-template <int NT>
+// k; a wave keeps U 16-byte loads of L (32 U k of its 16 rows) in flight, for U
+// = 16 a whole 128 KB tile over the work-group at m = 4096, and takes the token
+// operands (read by every work-group, so from L2) all (NT = 1) or half of them
+// (NT = 2) ahead.  The waves' sums are added in wave order through LDS.  8
+// tokens, m = 4096, 4096 columns: 11 us (3.0 TB/s; 19 us on 128 x 64 tiles).
+template <int NT, int U>
 __global__ __launch_bounds__(kThreads, 1) void append_few(
     const bf16* __restrict__ x, const bf16* __restrict__ LkT, const bf16* __restrict__ LvT,
     const int64_t* __restrict__ slot, bf16* __restrict__ pool, int n_tok, int m, int RK, int RKp,
     int rv, int64_t page_elems, int64_t value_base, int64_t num_pages) {
-  constexpr int U = 16, SB = U / NT;                   // L loads in flight; steps of a token batch
+  constexpr int SB = U / NT;                           // steps of a token batch
   __shared__ floatx4_t red[8][NT][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -412,7 +411,7 @@ __global__ __launch_bounds__(kThreads, 1) void append_few(
   floatx4_t acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  auto at = [&](int st) { return 32 * min(st, nst - 1) + 8 * lq; };   // clamped: in bounds
+  auto at = [&](int st) { return 32 * min(st, s1 - 1) + 8 * lq; };    // past the share: its last step again
   u32x4_t lv[U], xv[2][SB][NT];
   auto xload = [&](int set, int st) {
 #pragma unroll
@@ -462,16 +461,31 @@ __global__ __launch_bounds__(kThreads, 1) void append_few(
   }
 }
 
-template <int NT>
+template <int NT, int U>
 hipError_t launch_append_few(const dckv_plan& p, const void* x, int32_t n_tok, const void* Lk,
                              const void* Lv, const int64_t* slot, void* pool, int64_t num_pages,
                              hipStream_t stream) {
   const int ncols = p.RKp + p.rv;
-  hipLaunchKernelGGL(append_few<NT>, dim3((ncols + 15) / 16), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL((append_few<NT, U>), dim3((ncols + 15) / 16), dim3(kThreads), 0, stream,
                      static_cast<const bf16*>(x), static_cast<const bf16*>(Lk),
                      static_cast<const bf16*>(Lv), slot, static_cast<bf16*>(pool), n_tok, p.m,
                      p.RK, p.RKp, p.rv, p.page_elems, p.value_base, num_pages);
   return hipGetLastError();
+}
+
+// U: a wave's share of the 32-k steps, as a power of two up to 16.  Loads past
+// the share cost their issue: 32 tokens, 4096 columns take 4.2 us at m = 512
+// with U = 2 (13.2 with 16; 9.3 on 128 x 64 tiles), 5.5 at m = 1024 with 4
+// (13.4; 11.2), 8.0 at m = 2048 with 8 (13.3; 14.8).
+template <int NT>
+hipError_t launch_append_few(const dckv_plan& p, const void* x, int32_t n_tok, const void* Lk,
+                             const void* Lv, const int64_t* slot, void* pool, int64_t num_pages,
+                             hipStream_t stream) {
+  const int steps = (p.m / 32 + 7) / 8;
+  if (steps <= 2) return launch_append_few<NT, 2>(p, x, n_tok, Lk, Lv, slot, pool, num_pages, stream);
+  if (steps <= 4) return launch_append_few<NT, 4>(p, x, n_tok, Lk, Lv, slot, pool, num_pages, stream);
+  if (steps <= 8) return launch_append_few<NT, 8>(p, x, n_tok, Lk, Lv, slot, pool, num_pages, stream);
+  return launch_append_few<NT, 16>(p, x, n_tok, Lk, Lv, slot, pool, num_pages, stream);
 }
 
 // fp32 latents on the fp32 matrix instruction (m a multiple of 16): fp32
@@ -510,9 +524,10 @@ __global__ __launch_bounds__(256) void append_f32(const float* __restrict__ x,
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   floatx4_t v[U][4];
-  auto load = [&](int k, int st) {                     // clamped: in bounds
+  const int last = max(s1, 1) - 1;                     // past the share: its last step again
+  auto load = [&](int k, int st) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[k][i] = *reinterpret_cast<const floatx4_t*>(src[i] + 16 * min(st, nst - 1));
+    for (int i = 0; i < 4; ++i) v[k][i] = *reinterpret_cast<const floatx4_t*>(src[i] + 16 * min(st, last));
   };
 #pragma unroll
   for (int k = 0; k < U; ++k) load(k, s0 + k);

@@ -476,6 +476,32 @@ def test_append_at_tile_edges(n):
         assert np.all(Zg[untouched] == 0)
 
 
+# few tokens: 32-k steps that give the eight waves no, equal and unequal shares,
+# each number of loads in flight (2, 4, 8, 16) with full and partial shares, and
+# shares longer than the loads in flight (m = 4160).  Same bound as above.
+@pytest.mark.parametrize("n", [5, 30])
+@pytest.mark.parametrize("m", [64, 512, 704, 1024, 1984, 2048, 2112, 4096, 4160])
+def test_append_of_few_tokens_at_every_width(n, m):
+    from paper_2607_24331_amd import Plan, latent_append
+    from workloads.inputs import to_storage
+    ranks, rv = (37, 50), 61
+    plan = Plan(m, 4, 4, 64, (0, 1, 1, 0), ranks, rv)
+    g = np.random.default_rng(n + m)
+    x = to_storage(g.standard_normal((n, m)), "bf16")
+    Lk = to_storage(g.standard_normal((m, sum(ranks))) / np.sqrt(m), "bf16")
+    Lv = to_storage(g.standard_normal((m, rv)) / np.sqrt(m), "bf16")
+    slots = g.permutation(128)[:n].astype(np.int64)
+    pool = plan.new_pool(2)
+    latent_append(plan, dev(x, "bf16"), dev(Lk.T, "bf16"), dev(Lv.T, "bf16"),
+                  torch.from_numpy(slots).cuda(), pool)
+    Zk, Zv = olayout.unpack(pool.float().cpu().numpy(), np.arange(2, dtype=np.int32)[None, :], 0, 128,
+                            sum(ranks), rv)
+    for Zg, L in ((Zk, Lk), (Zv, Lv)):
+        rounded = obf16.round_to_bf16(oappend.down_project(x, L))
+        bound = obf16.ulp_bf16(rounded) + m * 2.0 ** -24 * oappend.abs_bound(x, L)
+        assert np.all(np.abs(Zg[slots] - rounded) <= bound)
+
+
 # fp32 latents: the matrix kernel at the edges of its 32 x 32 tiles and with
 # fewer 16-wide k steps than waves (m = 48), and the portable kernel where m is
 # not a multiple of 16 (m = 200); the fp32 dot-product bound of any order
