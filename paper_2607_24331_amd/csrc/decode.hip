@@ -446,11 +446,8 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context,
     // compute units without work (split kernel 370 us, balanced 292).  The
     // line does not lie at a batch: the host does not know the lengths, and
     // whole calls on a 32/8-head layer over lengths of an eighth to the whole
-    // of 131072 / batch tokens go 74.6 -> 69.6 us at 2 sequences, 70.0 -> 61.1
-    // at 4, 80.3 -> 70.1 at 16, 90.3 -> 80.1 at 64, while equal lengths pay
-    // for the record's load before all others: 88.3 -> 89.2 at 2, 88.1 ->
-    // 89.4 at 4, 95.7 -> 96.8 at 16, 102.2 -> 102.8 at 64.  One sequence is
-    // cut evenly as it is.
+    // of 131072 / batch tokens go 74.3 -> 72.6 us at 4 sequences, 81.3 -> 73.0
+    // at 16, 90.3 -> 80.1 at 64.  One sequence is cut evenly as it is.
     if (!plain && p.split_tokens == 0 && batch >= 2 && batch <= kSchedMaxBatch && units <= kSchedMaxUnits &&
         (p.dh == 64 || p.dh == 128)) {
       const int64_t npm = (int64_t(max_context) + DCKV_PAGE_TOKENS - 1) / DCKV_PAGE_TOKENS;
@@ -459,6 +456,20 @@ DecodeShape decode_shape(const dckv_plan& p, int32_t batch, int32_t max_context,
       int64_t U = units;
       const int64_t whole = U / target * target;
       if (whole >= batch && int64_t(batch) * ((npm + cap - 1) / cap) <= whole) U = whole;
+      // The fixed cut itself, which needs no record, where every sequence has
+      // at least this many pages: all its splits less a page each (no cut into
+      // as many splits is shorter), or five eighths of them where a sequence
+      // has 24 splits or more.  The call is bound by memory, so that compute
+      // units without a split cost nothing while enough others have one in
+      // every XCD; with fewer splits a sequence the short ones' missing splits
+      // are the same XCDs'.  32/8-head layer, lengths from the given part of
+      // 131072 / batch tokens on, fixed / balanced, us: 4 sequences 0.4: 81.7 /
+      // 80.1, 0.5: 82.3 / 82.9, 0.7: 85.7 / 87.4; 8: 0.5: 82.4 / 81.1, 0.6:
+      // 83.7 / 84.8, 0.8: 87.4 / 88.6; 16: 0.6: 90.0 / 86.5, 0.8: 94.2 / 92.8.
+      const int64_t Lp = L / DCKV_PAGE_TOKENS;
+      int64_t least = s.n_split * (Lp - 1) + 1;
+      if (s.n_split >= 24) least = std::min(least, (5 * s.n_split * Lp + 7) / 8);
+      s.fixed_pages = U == units ? int32_t(least) : INT32_MAX;
       s.n_sched = int32_t(U);
       s.n_units = int32_t((U + 7) / 8 * 8);
       s.off_sched = s.bytes;

@@ -158,6 +158,12 @@ __global__ __launch_bounds__(64) void fold_blocks(const float* __restrict__ q,
 // round trip: 64 lengths are tried at once, one a lane, from the least
 // possible on, and the units find their sequences by a scan over the first
 // units' marks.
+// Where every sequence has at least fixed_pages pages the fixed cut is taken
+// and no record is written: the split kernel makes the same test of the
+// lengths beside its first loads and waits for no record.
+__device__ __forceinline__ bool fixed_fits(int len, int max_context, int fixed_pages) {
+  return (min(len, max_context) + 63) >> 6 >= fixed_pages;       // fixed_pages >= 1
+}
 __device__ __forceinline__ int ceil_div(int n, int d, float inv) {   // n < 2^24
   int q = int(float(n) * inv);
   q -= q * d > n ? 1 : 0;
@@ -177,14 +183,25 @@ __device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
   __shared__ int len_lds[kSchedMaxBatch], first[kSchedMaxBatch], owner[kSchedMaxUnits];
   const int lane = threadIdx.x;
   int np[N], pages = 0;                      // pages < 2^25 a sequence, < 2^17 units of 2^8 in all
+  bool fits = true;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
     const int b = lane * N + k;
     const int t = sa.seq_lens[min(b, batch - 1)];
     const int len = b < batch ? max(0, min(t, sa.max_context)) : 0;
+    fits &= fixed_fits(t, sa.max_context, sa.fixed_pages);
     np[k] = (len + 63) >> 6;
     len_lds[b] = len;
     pages += np[k];
+  }
+  if (__all(fits)) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int b = lane * N + k;
+      if (b < batch)
+        sa.seqs[b] = SchedSeq{b * sa.n_split, (np[k] + sa.split_pages - 1) / sa.split_pages};
+    }
+    return;
   }
 #pragma unroll
   for (int k = 0; k < M; ++k) owner[lane + 64 * k] = 0;
@@ -253,15 +270,19 @@ __device__ __forceinline__ void cut_sequences(const SchedArgs& sa, int batch) {
 // lo parts (two products a k step), accumulated in fp32.  Columns outside
 // the head's group latent, and slots without a head, are written as zero.
 // d_h a multiple of 32 (KS = d_h / 32 k steps).
-template <int KS>
+// SCHED: one work-group more, the first, cuts the balanced splits (by template
+// and not by argument: a load of it would come before all others).
+template <int KS, bool SCHED>
 __global__ __launch_bounds__(64) void fold_mfma(const float* __restrict__ q,
                                                 const bf16* __restrict__ Rk,
                                                 u32x4* __restrict__ qblk_ws, int batch, float scale,
                                                 HeadTables tb, MfmaTables mt, SchedArgs sa) {
   int id = blockIdx.x;
-  if (sa.units && --id < 0) {                 // one work-group more, the first, cuts the balanced splits
-    cut_sequences(sa, batch);
-    return;
+  if constexpr (SCHED) {
+    if (--id < 0) {
+      cut_sequences(sa, batch);
+      return;
+    }
   }
   const int J = mt.n_slices;
   // 1-D grid, XCD-aware: the 16 slots of one (slice, chunk) write
@@ -378,7 +399,8 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
     const int32_t* __restrict__ page_table, int max_pages, const int32_t* __restrict__ seq_lens,
     int max_context, int split_tokens, int n_split, int n_units, int RK, int rv,
     int64_t page_elems, int64_t value_base, float* __restrict__ part_ml, float* __restrict__ part,
-    MfmaTables mt, const bf16* __restrict__ pw, const SchedUnit* __restrict__ sched) {
+    MfmaTables mt, const bf16* __restrict__ pw, const SchedUnit* __restrict__ sched, int batch,
+    int fixed_pages) {
   constexpr int NH = 16 * NT;                          // head slots of the slice
   constexpr int SW = (4 * NT < W) ? 4 * NT : W;        // waves holding score tiles
   constexpr int MPW = (4 * NT) / SW;                   // score M-tiles (16 tokens) a scoring wave
@@ -398,15 +420,14 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   const int u = grp * 8 + (rr % 8);       // all slices of unit u share an XCD (ids equal mod 8)
   if (u >= n_units) return;               // n_units = batch * n_split, or the balanced splits (the grid is padded)
   // fixed splits: sequence and first page by number; balanced ones (SCHED) by
-  // the unit's record, which also holds what the first loads of latents need
-  // (the page and the number of tokens), so that they wait for it alone
-  SchedUnit un = {0, 0, 0, 0};
-  if constexpr (SCHED) {
-    un = sched[u];
-    if (un.tokens == 0) return;           // fewer splits than units
-  }
-  const int b = SCHED ? un.b : u / n_split, split = SCHED ? 0 : u % n_split;
-  const int page0 = SCHED ? un.page0 : split * (split_tokens >> 6);
+  // the unit's record where the cut is another than the fixed one.  The loads
+  // below start with the fixed cut's numbers, beside those that tell which cut
+  // it is: 4 sequences of 32768 tokens on the 32/8-head layer take 88.0 us
+  // with fixed splits alone, 89.5 where every load waits for the record, 88.5
+  // so.
+  int b = u / n_split;
+  const int split = u - b * n_split;
+  int page0 = split * (split_tokens >> 6);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, provably uniform
   const int lr = lane & 15, lq = lane >> 4;
@@ -431,23 +452,50 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   // the later loads in flight.
   // (every load is unconditional at a clamped, valid address, so no branch
   // hides a load from the wait counting; unused values are dropped)
+  const int len_lane = SCHED ? seq_lens[min(int(threadIdx.x & 63), batch - 1)] : 0;
   constexpr int SWc = (4 * NT < W) ? 4 * NT : W;
   const int hrow_raw = mt.hord[slice][min(16 * ((min(w, SWc - 1) * ((4 * NT) / SWc)) / 4) + lr, kSliceHeads - 1)];
   const int hrow = w < SWc ? hrow_raw : -1;
   const int n16 = npairs * 128;
-  const int pg_lane = page_table[int64_t(b) * max_pages + min(page0 + tid, max_pages - 1)];
+  int pg_lane = page_table[int64_t(b) * max_pages + min(page0 + tid, max_pages - 1)];
   const u32x4* qsrc = qblk_ws + int64_t(b * J + slice) * mt.max_pairs * 128;
   u32x4 qv[kQblkLoads];
   if constexpr (!PW) {
 #pragma unroll
     for (int k = 0; k < kQblkLoads; ++k) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
   }
-  int pid0 = SCHED ? un.pid : page0 < max_pages ? page_table[int64_t(b) * max_pages + page0] : -1;
-  int T_b = seq_lens[b];
+  int pid0 = page0 < max_pages ? page_table[int64_t(b) * max_pages + page0] : -1;
+  int T_b = seq_lens[b];                  // clamped where it is used
+  bool fixed = true;
+  int t1 = 0;
+  if constexpr (SCHED) {
+    const int rec = reinterpret_cast<const int*>(sched + u)[lane & 3];   // a lane load: not waited for unless used
+    bool fits = fixed_fits(len_lane, max_context, fixed_pages);
+    for (int k = 64; k < batch; k += 64)
+      fits &= fixed_fits(seq_lens[min(lane + k, batch - 1)], max_context, fixed_pages);
+    fixed = __all(fits);
+    if (!fixed) {
+      // the record also holds what the first loads of latents need (the page
+      // and the number of tokens), so that they wait for it alone
+      const int b_fixed = b;
+      b = __builtin_amdgcn_readlane(rec, 0);
+      page0 = __builtin_amdgcn_readlane(rec, 1);
+      const int tokens = __builtin_amdgcn_readlane(rec, 2);
+      pid0 = __builtin_amdgcn_readlane(rec, 3);
+      if (tokens == 0) return;            // fewer splits than units
+      t1 = 64 * page0 + tokens;
+      pg_lane = page_table[int64_t(b) * max_pages + min(page0 + tid, max_pages - 1)];
+      if (b != b_fixed) {
+        qsrc = qblk_ws + int64_t(b * J + slice) * mt.max_pairs * 128;
+#pragma unroll
+        for (int k = 0; k < kQblkLoads; ++k) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
+      }
+      T_b = seq_lens[b];
+    }
+  }
   const int t0 = 64 * page0;
   pid0 = __builtin_amdgcn_readfirstlane((pid0 >= 0 && pid0 < num_pages) ? pid0 : -1);
-  T_b = T_b < 0 ? 0 : (T_b > max_context ? max_context : T_b);
-  const int t1 = SCHED ? t0 + un.tokens : min(t0 + split_tokens, T_b);
+  if (fixed) t1 = min(t0 + split_tokens, max(0, min(T_b, max_context)));
   if (t0 >= t1) return;                   // the merge only reads splits holding tokens
   const int np = (t1 - t0 + 63) / 64;
 
@@ -479,6 +527,7 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
                     : -1;
   // causal limit of this lane's score column: query i of Q sits at position
   // T_b - Q + i and sees the positions before it and its own
+  T_b = max(0, min(T_b, max_context));
   int lim = T_b;
   if (scoring && hrow >= 0) lim = T_b - mt.queries + hrow / mt.q_heads + 1;
   const int kvalid_last = min(8, max(0, RK - (32 * kc_last + 8 * lq)));
@@ -1019,7 +1068,7 @@ hipError_t launch_split(const dckv_plan& p, const MfmaTables& mt, const DecodeSh
                          static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
                          sh.max_context, sh.split_tokens, sh.n_split, sh.batch * sh.n_split,
                          p.RK, p.rv, p.page_elems, p.value_base, part_ml, part, mt, pw,
-                         static_cast<const SchedUnit*>(nullptr));
+                         static_cast<const SchedUnit*>(nullptr), 0, 0);
       return hipGetLastError();
     }
     return hipErrorInvalidValue;
@@ -1036,13 +1085,13 @@ hipError_t launch_split(const dckv_plan& p, const MfmaTables& mt, const DecodeSh
                           page_table, max_pages, seq_lens, sh.max_context, sh.split_tokens,
                           sh.n_split, n_units, p.RK, p.rv, p.page_elems,
                           p.value_base, part_ml, part, mt, static_cast<const bf16*>(nullptr),
-                          sched);
+                          sched, sh.batch, sh.fixed_pages);
   else
     hipLaunchKernelGGL(kern, dim3(grid), dim3(W * 64), lds, stream, qblk,
                        static_cast<const bf16*>(pool), num_pages, page_table, max_pages, seq_lens,
                        sh.max_context, sh.split_tokens, sh.n_split, n_units, p.RK,
                        p.rv, p.page_elems, p.value_base, part_ml, part, mt,
-                       static_cast<const bf16*>(nullptr), sched);
+                       static_cast<const bf16*>(nullptr), sched, sh.batch, sh.fixed_pages);
   return hipGetLastError();
 }
 
@@ -1137,7 +1186,8 @@ hipError_t launch_fold(const dckv_plan& p, const MfmaTables& mt, int32_t batch, 
   // d_h 64 or 128: one wave a (slice, slot, chunk) for all sequences, on
   // MFMA; other head sizes: one wave a (sequence, slice, slot, chunk)
   if (p.dh == 64 || p.dh == 128) {
-    auto kern = p.dh == 64 ? fold_mfma<2> : fold_mfma<4>;
+    auto kern = sched.units ? (p.dh == 64 ? fold_mfma<2, true> : fold_mfma<4, true>)
+                            : (p.dh == 64 ? fold_mfma<2, false> : fold_mfma<4, false>);
     const int ngrp = mt.n_slices * mt.max_pairs;
     hipLaunchKernelGGL(kern, dim3(8 * 16 * ((ngrp + 7) / 8) + (sched.units ? 1 : 0)), dim3(64), 0,
                        stream, q, static_cast<const bf16*>(R_keys), static_cast<u32x4*>(qblk), batch,
@@ -1180,6 +1230,9 @@ hipError_t launch_decode_mfma(const dckv_plan& p, const DecodeShape& sh, const f
     sa.max_pages = max_pages;
     sa.max_context = sh.max_context;
     sa.n_units = sh.n_sched;
+    sa.n_split = sh.n_split;
+    sa.fixed_pages = sh.fixed_pages;
+    sa.split_pages = sh.split_tokens / DCKV_PAGE_TOKENS;
     sa.units = reinterpret_cast<SchedUnit*>(ws + sh.off_sched);
     sa.seqs = reinterpret_cast<SchedSeq*>(sa.units + sh.n_sched);
   }

@@ -94,6 +94,7 @@ struct DecodeShape {
   // balanced splits (single-pass path, several sequences, automatic split size):
   // the fold kernel cuts the sequences' actual pages into n_sched splits
   int32_t n_sched;          // splits (grid units) in all, 0: fixed splits of split_tokens
+  int32_t fixed_pages;      // with this many pages of every sequence they are the fixed cut
   size_t off_sched;         // workspace: n_sched unit records, then a record a sequence
   size_t sched_bytes;       // its size
   // two-pass path
@@ -117,8 +118,9 @@ struct DecodeShape {
 };
 
 // Balanced splits: unit u takes `tokens` tokens of sequence b from page page0
-// on, whose entry in the page table is pid (tokens 0: nothing); sequence b's
-// units are u0 .. u0 + units - 1.
+// on, whose entry in the page table is pid (tokens 0: nothing; no record is
+// written where the cut is the fixed one); sequence b's units are u0 .. u0 +
+// units - 1.
 struct SchedUnit {
   int32_t b, page0, tokens, pid;
 };
@@ -133,6 +135,7 @@ struct SchedArgs {
   const int32_t* seq_lens;
   const int32_t* page_table;
   int32_t max_pages, max_context, n_units;
+  int32_t n_split, split_pages, fixed_pages;   // the fixed cut
   SchedUnit* units;
   SchedSeq* seqs;
 };

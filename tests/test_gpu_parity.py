@@ -401,43 +401,62 @@ def test_value_halves(rv, heads, lens, Q):
     assert max(errs) <= TOL_REL_ROW
 
 
-# balanced splits: a short and a long sequence, empty ones, equal lengths,
-# lengths beyond max_context, as many sequences as one wave cuts (256) and one
-# more (fixed splits), several queries (two row slices)
+# balanced splits, every row against the oracle: a short and a long sequence,
+# empty ones, lengths beyond max_context, as many sequences as one wave cuts
+# (256) and one more (fixed splits), several queries (two row slices).  "fixed"
+# where every sequence has the pages for which the fixed cut is kept (64 tokens
+# a split; all splits less a page; five eighths of 105 splits of three pages,
+# 197 pages, and one token less; two splits of eight pages): the same bits as
+# with that split size asked for.
 SCHED = {
-    "short_and_long": ((1, 20001), 1), "ragged": (tuple((97 * i * i) % 1500 for i in range(40)), 1),
-    "equal": ((640,) * 8, 1), "empty": ((0, 0, 0), 1), "one_used": ((0, 5000, 0, 0), 1),
-    "beyond": ((300, 900, 5000), 1), "b256": (tuple((i * 37) % 200 for i in range(256)), 1),
-    "b257": (tuple((i * 37) % 200 for i in range(257)), 1),
-    "queries": ((2000, 130, 64, 777), 8),
+    "short_and_long": ((1, 20001), 1, False), "ragged": (tuple((97 * i * i) % 1500 for i in range(40)), 1, False),
+    "equal": ((640,) * 8, 1, True), "empty": ((0, 0, 0), 1, False), "one_used": ((0, 5000, 0, 0), 1, False),
+    "beyond": ((300, 900, 5000), 1, True), "b256": (tuple((i * 37) % 200 for i in range(256)), 1, False),
+    "b257": (tuple((i * 37) % 200 for i in range(257)), 1, True),
+    "queries": ((2000, 130, 64, 777), 8, True),
+    "equal_long": ((20001,) * 2, 1, True), "five_eighths": ((20001, 196 * 64 + 1), 1, True),
+    "below_five_eighths": ((20001, 196 * 64), 1, False),
+    "b128": ((1024,) * 128, 1, True), "b128_one_short": ((1024,) * 126 + (100, 1024), 1, False),
 }
 
 
 @pytest.mark.parametrize("name", list(SCHED))
 def test_balanced_splits(name):
+    from oracle.bookkeeping import make_book
     from paper_2607_24331_amd import Plan, decode
-    lens, Q = SCHED[name]
+    lens, Q, fixed = SCHED[name]
     B, top = len(lens), 1000 if name == "beyond" else max(max(lens), 64)
     layer = (512, 8, 4, 64, (0, 1, 1, 0), (60, 45), 144)
     g = torch.Generator(device="cuda")
     g.manual_seed(len(lens))
     rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
-    auto, fixed = (Plan(*layer, split_tokens=sp, queries_per_seq=Q) for sp in (0, 256))
+    auto = Plan(*layer, queries_per_seq=Q)
+    cut = auto.launch_info(B, top)["split_tokens"]
     pages = -(-top // 64)
     pool = rnd(B * pages, auto.page_elems).to(torch.bfloat16)
     table = torch.randperm(B * pages, generator=g, device="cuda").to(torch.int32).view(B, pages)
-    args = (rnd(B, Q, 8, 64), pool, table, torch.tensor(lens, dtype=torch.int32, device="cuda"), top,
-            (rnd(auto.key_factor_elems) / 8).to(torch.bfloat16), (rnd(144, 256) / 16).to(torch.bfloat16))
-    a, b, again = decode(auto, *args), decode(fixed, *args), decode(auto, *args)
+    q = rnd(B, Q, 8, 64)
+    Rk = (rnd(auto.key_factor_elems) / 8).to(torch.bfloat16)
+    Rv = (rnd(144, 256) / 16).to(torch.bfloat16)
+    args = (q, pool, table, torch.tensor(lens, dtype=torch.int32, device="cuda"), top, Rk, Rv)
+    a, again = decode(auto, *args), decode(auto, *args)
     assert torch.equal(a, again)                              # bitwise repeatable
-    assert torch.isfinite(a).all()
-    # the splits change the order of fp32 sums and which rounding a bf16 weight
-    # gets (2^-9 of a row's largest value at most, each way)
-    scale = b.abs().amax(dim=-1, keepdim=True).clamp_min(1e-30)
-    assert float(((a - b).abs() / scale).max()) <= 2.0 ** -7
-    for s, n in enumerate(lens):
-        if n == 0:
-            assert float(a[s].abs().max()) == 0
+    if fixed:
+        assert torch.equal(a, decode(Plan(*layer, split_tokens=cut, queries_per_seq=Q), *args))
+    blocks = np.split(Rk.float().cpu().numpy(), [60 * 128])
+    seen = [min(n, top) for n in lens]
+    got = a.cpu().numpy().astype(np.float64).reshape(B, Q, 8, 64)
+    ref = oattn.decode_multi(q.cpu().numpy(), pool.float().cpu().numpy(), table.cpu().numpy(), seen,
+                             [blocks[0].reshape(60, 128), blocks[1].reshape(45, 128)],
+                             Rv.float().cpu().numpy(), make_book(*layer), chunk=None)
+    errs = []
+    for b in range(B):
+        for i in range(Q):
+            if oattn.visible_tokens(seen[b], Q, i) == 0:
+                assert np.all(got[b, i] == 0)
+            else:
+                errs += [row_rel_err(got[b, i, h], ref[b, i, h]) for h in range(8)]
+    assert max(errs, default=0.0) <= TOL_REL_ROW
 
 
 # each kernel of the append at the edges of its tiles: 1 to 32 tokens (one and
