@@ -401,6 +401,34 @@ def test_value_halves(rv, heads, lens, Q):
     assert max(errs) <= TOL_REL_ROW
 
 
+# two value slices over splits of two pages: the weights of a page are relative
+# to the page's maximum, so they are bit for bit those of one-page splits and
+# only fp32 sums differ (below 2^-20 of a row; the weights' roundings are 1.4e-3)
+def test_value_halves_lose_no_precision():
+    from oracle.bookkeeping import make_book
+    from paper_2607_24331_amd import Plan, decode
+    layer = (2048, 12, 12, 128, (0, 1, 2) * 4, (150, 120, 90), 1411)
+    B, T = 4, 4096
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    auto, single = Plan(*layer), Plan(*layer, split_tokens=64)
+    assert auto.launch_info(B, T)["split_tokens"] == 128
+    pool = rnd(B * T // 64, auto.page_elems).to(torch.bfloat16)
+    table = torch.randperm(B * T // 64, generator=g, device="cuda").to(torch.int32).view(B, -1)
+    q, lens = rnd(B, 12, 128), torch.full((B,), T, dtype=torch.int32, device="cuda")
+    Rk = (rnd(auto.key_factor_elems) / 512 ** 0.5).to(torch.bfloat16)
+    Rv = (rnd(1411, 1536) / 1536 ** 0.5).to(torch.bfloat16)
+    args = (q, pool, table, lens, T, Rk, Rv)
+    a, b = (decode(p, *args).cpu().numpy().astype(np.float64) for p in (auto, single))
+    Rk = Rk.float().cpu().numpy()
+    blocks = [x.reshape(r, 512) for x, r in zip(np.split(Rk, [150 * 512, 270 * 512]), (150, 120, 90))]
+    ref = oattn.decode_multi(q.cpu().numpy()[:, None], pool.float().cpu().numpy(), table.cpu().numpy(),
+                             [T] * B, blocks, Rv.float().cpu().numpy(), make_book(*layer), chunk=None)[:, 0]
+    ea, eb = np.linalg.norm(a - ref), np.linalg.norm(b - ref)
+    assert ea <= 1.002 * eb
+
+
 # balanced splits, every row against the oracle: a short and a long sequence,
 # empty ones, lengths beyond max_context, as many sequences as one wave cuts
 # (256) and one more (fixed splits), several queries (two row slices).  "fixed"
