@@ -1567,16 +1567,6 @@ size_t upproj_wide_lds_bytes(const dckv_plan& p, int rows, int rb) {
 hipError_t launch_upproj(const dckv_plan& p, int32_t batch_rows, const float* amerged,
                          const void* R_value, float* out, hipStream_t stream) {
   const int rows = batch_rows * p.qpk;          // rows a KV head
-  // from three rows on and a long contraction: the one-round-trip kernel
-  // (32 KV heads of 128, r_v 2048: 4 rows 13.2 -> 9.9 us, 8 rows 12.7 -> 9.8;
-  // r_v 1536, 64 rows 24.2 -> 21.3; with 8 KV heads, r_v 768, 16 rows, its
-  // few large work-groups start later than they save: 6.7 -> 8.7)
-  if (rows >= 3 && p.rv >= 1024 && p.dh % 32 == 0) {
-    const int per = (p.dh / 32) * ((rows + 15) / 16);
-    hipLaunchKernelGGL(upproj_tr, dim3(8 * ((p.Hkv + 7) / 8) * per), dim3(kUpWaves * 64), 0, stream,
-                       amerged, static_cast<const bf16*>(R_value), out, rows, p.rv, p.tables);
-    return hipGetLastError();
-  }
   // one or two rows a KV head, with 64-column tiles that give the grid at
   // least 32 work-groups: the wide kernel (whole 128-byte pieces of R_v;
   // from three rows on its per-lane products cost more than the MFMA
@@ -1598,11 +1588,32 @@ hipError_t launch_upproj(const dckv_plan& p, int32_t batch_rows, const float* am
   // and the VALU kernels read it straight into registers): 32-column tiles
   // while the transposed R_v block fits LDS and the grid still fills the
   // chip, else 16
-  const int groups = p.Hkv * ((rows + 63) / 64);
+  const int ngr = p.Hkv * ((rows + 63) / 64);
   const bool fit32 = p.dh % 32 == 0 && upproj_mfma_lds_bytes(p, 32) <= 160 * 1024;
   const bool fit16 = p.dh % 16 == 0 && upproj_mfma_lds_bytes(p, 16) <= 160 * 1024;
   const int ctm = rows < 3 ? 0
-                  : (fit32 && (groups * (p.dh / 32) >= 256 || !fit16)) ? 32 : (fit16 ? 16 : 0);
+                  : (fit32 && (ngr * (p.dh / 32) >= 256 || !fit16)) ? 32 : (fit16 ? 16 : 0);
+  // For a long contraction the one-round-trip kernel while its work-groups, of
+  // sixteen rows and one a compute unit, take at most two rounds over the chip
+  // for one of the MFMA kernel's, which read R_v once for 64 rows.  Measured,
+  // MFMA / one round trip, us, d_h 128: 32 KV heads, r_v 2048, 4 rows 10.7 /
+  // 7.4, 16: 11.9 / 9.2, 32: 17.2 / 10.2, 64 (two rounds) 24.9 / 20.3, 96
+  // (three) 25.7 / 27.4, 128: 25.9 / 37.5; r_v 1152, 64 rows 17.8 / 17.5; 20
+  // heads, r_v 1152, 128 rows (three for two) 31.5 / 25.7.  Below r_v 1152 a
+  // second round for one and a nearly full tile of rows cost more than they
+  // save: 32 heads, r_v 1024, 33 rows 13.7 / 15.2; 8 to 24 heads, 16 rows 7.5 /
+  // 7.9 (8 heads, 3 rows 6.8 / 6.1, 32 rows 10.6 / 8.1).  With 8 heads, r_v 768,
+  // 16 rows, its few large work-groups start later than they save: 6.7 / 8.7.
+  if (ctm && p.rv >= 1024 && p.dh % 32 == 0) {
+    const int per = (p.dh / 32) * ((rows + 15) / 16);
+    const int rounds = (p.Hkv * per + 255) / 256, rounds_mfma = (ngr * (p.dh / ctm) + 255) / 256;
+    if (p.rv >= 1152 ? rounds <= 2 * rounds_mfma
+                     : 2 * rounds <= 3 * rounds_mfma && (rows <= 12 || rows > 16)) {
+      hipLaunchKernelGGL(upproj_tr, dim3(8 * ((p.Hkv + 7) / 8) * per), dim3(kUpWaves * 64), 0, stream,
+                         amerged, static_cast<const bf16*>(R_value), out, rows, p.rv, p.tables);
+      return hipGetLastError();
+    }
+  }
   if (ctm) {
     const size_t lds = upproj_mfma_lds_bytes(p, ctm);
     // eight waves when four would each walk 32 rank steps or more
@@ -1613,7 +1624,6 @@ hipError_t launch_upproj(const dckv_plan& p, int32_t batch_rows, const float* am
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    const int ngr = p.Hkv * ((rows + 63) / 64);
     hipLaunchKernelGGL(kern, dim3(8 * ((ngr + 7) / 8) * (p.dh / ctm)), dim3(W * 64), lds, stream,
                        amerged, static_cast<const bf16*>(R_value), out, rows, p.rv, p.tables);
     return hipGetLastError();

@@ -354,8 +354,11 @@ def test_append_random_within_one_ulp():
 
 # the one-round-trip up-projection (three rows a KV head or more, value ranks
 # from 1024 on): ranks not a multiple of 4 or 32, above one round of 2048, rows
-# at the edges of 16-row tiles, KV heads not a multiple of 8
-@pytest.mark.parametrize("rv, batch, kv", [(1027, 3, 17), (1040, 17, 9), (1500, 33, 12), (2500, 4, 20)])
+# at the edges of 16-row tiles, KV heads not a multiple of 8; then two rounds of
+# its work-groups, and the MFMA kernel that takes over: a nearly full tile and a
+# second round below rank 1152, a third round (32-column tiles) above
+@pytest.mark.parametrize("rv, batch, kv", [(1027, 3, 17), (1040, 17, 9), (1500, 33, 12), (2500, 4, 20),
+                                           (1155, 40, 32), (1040, 14, 9), (1030, 40, 32), (1301, 80, 32)])
 def test_upproject_edges(rv, batch, kv):
     lens = tuple(1 + (29 * i) % 97 for i in range(batch))
     wl = custom_workload(name="up", seed=rv, hidden=2560, num_q_heads=kv, num_kv_heads=kv, head_dim=128,
