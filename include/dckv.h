@@ -187,15 +187,19 @@ int dckv_decode_workspace_bytes(const dckv_plan* plan, int32_t batch, int32_t ma
                                 size_t* bytes);
 
 /* The launch a dckv_decode call of `batch` sequences of at most
- * `max_context` tokens takes: which kernels, and how the context is cut
- * (it depends on the plan and these two numbers only). */
+ * `max_context` tokens takes: which kernels, and how the context is cut, as
+ * the host sees it from the plan and these two numbers.  Where the library
+ * chooses the split size (split_tokens 0) for 2 to 256 sequences of the
+ * single-pass kernel, d_h 64 or 128, the device keeps this cut while the
+ * sequences' lengths are alike and otherwise cuts them by their actual
+ * lengths, into no more splits in all.  (Whether the value part is taken in
+ * two slices is the library's choice too: half the partials, twice the split
+ * length.) */
 typedef struct dckv_launch_info {
   int32_t kernels;       /* 0 portable VALU kernels, 1 single-pass MFMA split kernel,
                             2 two-pass MFMA kernels */
-  int32_t split_tokens;  /* context tokens a split (a value chunk on the two-pass path);
-                            where the library cuts several sequences of the single-pass
-                            kernel by their actual lengths: the fixed cut it starts from */
-  int32_t n_split;       /* splits (chunks) of the longest sequence, likewise */
+  int32_t split_tokens;  /* context tokens a split (a value chunk on the two-pass path) */
+  int32_t n_split;       /* splits (chunks) of a sequence of max_context tokens */
   int32_t head_slices;   /* row slices of the MFMA kernels (each slice's score work
                             reads its groups' key chunks; on the single-pass kernel
                             each also reads the value part), 1 on the portable path */
@@ -243,9 +247,12 @@ int dckv_latent_append(const dckv_plan* plan, const void* x, int32_t n_tok,
  *   workspace   device scratch of at least dckv_decode_workspace_bytes(batch,
  *               max_context) bytes, 256-byte aligned; its contents on entry
  *               do not matter and are overwritten
- * Results are bitwise reproducible for a fixed plan and inputs: the work
- * split depends only on split_tokens or, where the library chooses it, on the
- * sequence lengths, and every reduction runs in a fixed order.  batch == 0 is a no-op; batch * Q is at most 65535. */
+ * Results are bitwise reproducible for a fixed plan and inputs: every
+ * reduction runs in a fixed order over a work split that depends on
+ * split_tokens or, where the library chooses it, on batch, max_context and the
+ * lengths of all sequences of the call (so another batch may round a
+ * sequence's result differently).  batch == 0 is a no-op; batch * Q is at most
+ * 65535. */
 int dckv_decode(const dckv_plan* plan, const float* q, int32_t batch, const void* pool,
                 int64_t num_pages, const int32_t* page_table, int32_t max_pages,
                 const int32_t* seq_lens, int32_t max_context, const void* R_keys,
@@ -365,10 +372,12 @@ int dckv_dense_decode(int32_t num_q_heads, int32_t num_kv_heads, int32_t head_di
  * of bf16 samples, exact in fp32, or of fp32 values (fp32 or centred samples)
  * taken as three bf16 parts each: exact for at most 32 rows, to below 2^-22 of
  * a product (2^-24 and less in the mean) for more, where the sums' own
- * roundings are larger.  A sample that is not finite makes its elements of G
- * infinite or NaN as products and sums of the values would, and the call
- * take at most twice as long.  Errors: DCKV_EINVAL (shape, null pointer), DCKV_EDTYPE,
- * DCKV_EALIGN, DCKV_EWORKSPACE, DCKV_EHIP; nothing is launched on error. */
+ * roundings are larger; values below 2^-110 in magnitude keep fewer bits, as
+ * the least parts then fall below bf16's range.  A sample that is not finite
+ * makes its elements of G infinite or NaN as products and sums of the values
+ * would, and the call take at most twice as long.  Errors: DCKV_EINVAL (shape,
+ * null pointer), DCKV_EDTYPE, DCKV_EALIGN, DCKV_EWORKSPACE, DCKV_EHIP; nothing
+ * is launched on error. */
 int dckv_gram_workspace_bytes(int64_t rows, int32_t cols, int32_t center, size_t* bytes);
 int dckv_gram(const void* A, int32_t dtype, int64_t rows, int32_t cols, int32_t center, float* G,
               void* workspace, size_t workspace_bytes, void* stream);
