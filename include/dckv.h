@@ -372,7 +372,7 @@ int dckv_dense_decode(int32_t num_q_heads, int32_t num_kv_heads, int32_t head_di
  * of bf16 samples, exact in fp32, or of fp32 values (fp32 or centred samples)
  * taken as three bf16 parts each: exact for at most 32 rows, to below 2^-22 of
  * a product (2^-24 and less in the mean) for more, where the sums' own
- * roundings are larger; values below 2^-110 in magnitude keep fewer bits, as
+ * roundings are larger; values below 2^-100 in magnitude keep fewer bits, as
  * the least parts then fall below bf16's range.  A sample that is not finite
  * makes its elements of G infinite or NaN as products and sums of the values
  * would, and the call take at most twice as long.  Errors: DCKV_EINVAL (shape,
