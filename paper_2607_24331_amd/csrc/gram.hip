@@ -417,6 +417,96 @@ __device__ __forceinline__ uint32_t class_of(float d) {
   return (u >> 16 & 0x8000u) | (m == 0 ? 0u : m < 0x7F800000u ? 0x3F80u : 0x7F80u);
 }
 
+// Infinities do not survive the split (inf has NaN for a rest, and inf times a
+// part that is 0 is NaN).  A tile that holds an element that is not finite
+// walks its samples once more and takes each as its class: 0, +-1 for a finite
+// value, +-inf, NaN.  Sums of products of classes are infinite or NaN where
+// those of the values are, and those elements are written again; where they
+// are finite the samples are too, and what was written is a sum that left
+// fp32's range.  One product a term: whatever the samples hold, less than the
+// walk before took.  Everything is worked out anew from the thread's number
+// (which the compiler is kept from recognising), so that none of it stays live
+// through the walk before: sharing its offsets cost that one up to 4 % (1387 x
+// 2048 bf16 samples, centred, 83.2 -> 86.7 us).
+template <typename T, int NS>
+__device__ __forceinline__ void gram_classes(const T* __restrict__ A, int64_t rows, int cols,
+                                             unsigned char* smem, float* __restrict__ G, int i0, int j0) {
+  constexpr int F = 2 * NS, OP = NS * 4096, BUF = 6 * OP, NQ = sizeof(T) / 2;
+  const float* smu = reinterpret_cast<const float*>(smem + 2 * BUF);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, w = tid >> 6, pos = w & 3, wi = pos >> 1, wj = pos & 1;
+  const int lq = lane >> 4, li = lane & 15;
+  const int crow = (tid & 255) >> 3, cpiece = tid & 7, nst = int((rows + 31) >> 5);
+  floatx4 acc[F][F];
+#pragma unroll
+  for (int x = 0; x < F; ++x)
+#pragma unroll
+    for (int y = 0; y < F; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
+  int oi[2], oj[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int sw = 2 * (lq & 1) + (li >> 3);
+    const int at = (4 * lq + (li >> 2)) * 128 + 8 * (li & 3);
+    oi[e] = at + 32 * ((2 * wi + e) ^ sw);
+    oj[e] = OP + at + 32 * ((2 * wj + e) ^ sw);
+  }
+  for (int st = 0; st < nst; ++st) {
+    __syncthreads();                                             // the stage before has been read
+    const int64_t r = int64_t(st) * 32 + crow;
+    const T* row = A + min(r, rows - 1) * cols;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      const int f = 2 * q + (w >> 2);
+      const int c0 = (f < NS ? i0 + 64 * f : j0 + 64 * (f - NS)) + 8 * cpiece;
+      u32x4 v[NQ], c;
+#pragma unroll
+      for (int k = 0; k < NQ; ++k) v[k] = reinterpret_cast<const u32x4*>(row + min(c0, cols - 8))[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float d0, d1;
+        if constexpr (NQ == 2) {
+          d0 = __uint_as_float(v[k >> 1][2 * (k & 1)]);
+          d1 = __uint_as_float(v[k >> 1][2 * (k & 1) + 1]);
+        } else {
+          d0 = __uint_as_float(v[0][k] << 16);
+          d1 = __uint_as_float(v[0][k] & 0xFFFF0000u);
+        }
+        d0 -= smu[64 * f + 8 * cpiece + 2 * k];
+        d1 -= smu[64 * f + 8 * cpiece + 2 * k + 1];
+        c[k] = r < rows ? class_of(d0) | class_of(d1) << 16 : 0u;
+      }
+      *reinterpret_cast<u32x4*>(smem + f * 4096 + crow * 128 + 16 * (cpiece ^ (crow & 6))) = c;
+    }
+    __syncthreads();
+    if (w < 4) {
+      short8_t a[F];
+#pragma unroll
+      for (int x = 0; x < F; ++x) a[x] = read_frag(smem + oi[x & 1] + (x >> 1) * 4096);
+#pragma unroll
+      for (int y = 0; y < F; ++y) {
+        const short8_t b = read_frag(smem + oj[y & 1] + (y >> 1) * 4096);
+#pragma unroll
+        for (int x = 0; x < F; ++x) acc[x][y] = mfma_bf16(a[x], b, acc[x][y]);
+      }
+    }
+  }
+  if (w >= 4) return;
+#pragma unroll
+  for (int x = 0; x < F; ++x)
+#pragma unroll
+    for (int y = 0; y < F; ++y) {
+      const int i = i0 + 64 * (x >> 1) + 32 * wi + 16 * (x & 1) + 4 * lq;
+      const int j = j0 + 64 * (y >> 1) + 32 * wj + 16 * (y & 1) + li;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (i < cols && j < cols && (i0 != j0 || i + v <= j) && !(fabsf(acc[x][y][v]) < INFINITY)) {
+          G[int64_t(j) * cols + i + v] = acc[x][y][v];
+          G[int64_t(i + v) * cols + j] = acc[x][y][v];
+        }
+    }
+}
+
 template <typename T, int NS, bool FEW = false>
 __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restrict__ A, int64_t rows,
                                                              int cols, const float* __restrict__ mu,
@@ -461,37 +551,31 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
 #pragma unroll
       for (int k = 0; k < NQ; ++k) raw[q][k] = *reinterpret_cast<const u32x4*>(base + goff[q] + 16 * k);
   };
-  // the loaded values of chunk q, zero past the last row: put(k, two of them)
-  auto values = [&](int st, int q, auto put) {
+  auto convert = [&](int st, unsigned char* buf) {               // zeros past the last row
     const bool live = int64_t(st) * 32 + crow < rows;
-    const floatx4 m0 = *reinterpret_cast<const floatx4*>(smu + moff[q]);
-    const floatx4 m1 = *reinterpret_cast<const floatx4*>(smu + moff[q] + 4);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float d0, d1;
-      if constexpr (NQ == 2) {
-        d0 = __uint_as_float(raw[q][k >> 1][2 * (k & 1)]);
-        d1 = __uint_as_float(raw[q][k >> 1][2 * (k & 1) + 1]);
-      } else {
-        d0 = __uint_as_float(raw[q][0][k] << 16);
-        d1 = __uint_as_float(raw[q][0][k] & 0xFFFF0000u);
-      }
-      d0 -= k < 2 ? m0[2 * k] : m1[2 * k - 4];
-      d1 -= k < 2 ? m0[2 * k + 1] : m1[2 * k - 3];
-      put(k, live ? d0 : 0.f, live ? d1 : 0.f);
-    }
-  };
-  auto convert = [&](int st, unsigned char* buf) {
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
+      const floatx4 m0 = *reinterpret_cast<const floatx4*>(smu + moff[q]);
+      const floatx4 m1 = *reinterpret_cast<const floatx4*>(smu + moff[q] + 4);
       u32x4 h, m, l;
-      values(st, q, [&](int k, float d0, float d1) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float d0, d1;
+        if constexpr (NQ == 2) {
+          d0 = __uint_as_float(raw[q][k >> 1][2 * (k & 1)]);
+          d1 = __uint_as_float(raw[q][k >> 1][2 * (k & 1) + 1]);
+        } else {
+          d0 = __uint_as_float(raw[q][0][k] << 16);
+          d1 = __uint_as_float(raw[q][0][k] & 0xFFFF0000u);
+        }
+        d0 -= k < 2 ? m0[2 * k] : m1[2 * k - 4];
+        d1 -= k < 2 ? m0[2 * k + 1] : m1[2 * k - 3];
         uint32_t ph, pm, pl;
-        split_pair(d0, d1, ph, pm, pl);
+        split_pair(live ? d0 : 0.f, live ? d1 : 0.f, ph, pm, pl);
         h[k] = ph;
         m[k] = pm;
         l[k] = pl;
-      });
+      }
       *reinterpret_cast<u32x4*>(buf + soff[q]) = h;
       *reinterpret_cast<u32x4*>(buf + PL + soff[q]) = m;
       *reinterpret_cast<u32x4*>(buf + 2 * PL + soff[q]) = l;
@@ -590,6 +674,7 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
         cross(smem + (st & 1) * BUF, std::integral_constant<int, 2 * PL>{}, std::false_type{});
         if (NS == 3) load(st + 1);             // later than need be: registers
         mid_mid(smem + (st & 1) * BUF);
+        __builtin_amdgcn_sched_barrier(0);     // not among the products (2 slabs: 84 -> 78 us at 1387 x 2048 bf16)
         convert(st + 1, smem + ((st + 1) & 1) * BUF);
         if (NS < 3) load(st + 2);
         __syncthreads();
@@ -597,55 +682,7 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_split(const T* __restric
     }
   }
   if (!__syncthreads_or(gram_write<NS>(acc, smem, G, cols, i0, j0, wi, wj, kh, pos, lane))) return;
-
-  // Infinities do not survive the split (inf has NaN for a rest, and inf times
-  // a part that is 0 is NaN).  A tile that holds an element that is not finite
-  // walks its samples once more and takes each as its class: 0, +-1 for a
-  // finite value, +-inf, NaN.  Sums of products of classes are infinite or NaN
-  // where those of the values are, and those elements are written again;
-  // where they are finite the samples are too, and what was written is a sum
-  // that left fp32's range.  One product a term: whatever the samples hold,
-  // less than the walk above took.
-#pragma unroll
-  for (int x = 0; x < F; ++x)
-#pragma unroll
-    for (int y = 0; y < F; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int st = 0; st < nst; ++st) {
-    __syncthreads();                                             // the stage before has been read
-    load(st);
-#pragma unroll
-    for (int q = 0; q < NS; ++q) {
-      u32x4 c;
-      values(st, q, [&](int k, float d0, float d1) { c[k] = class_of(d0) | class_of(d1) << 16; });
-      *reinterpret_cast<u32x4*>(smem + soff[q]) = c;
-    }
-    __syncthreads();
-    if (kh == 0) {
-      short8_t a[F];
-#pragma unroll
-      for (int x = 0; x < F; ++x) a[x] = read_frag(smem + oi[x & 1] + (x >> 1) * 4096);
-#pragma unroll
-      for (int y = 0; y < F; ++y) {
-        const short8_t b = read_frag(smem + oj[y & 1] + (y >> 1) * 4096);
-#pragma unroll
-        for (int x = 0; x < F; ++x) acc[x][y] = mfma_bf16(a[x], b, acc[x][y]);
-      }
-    }
-  }
-  if (kh != 0) return;
-#pragma unroll
-  for (int x = 0; x < F; ++x)
-#pragma unroll
-    for (int y = 0; y < F; ++y) {
-      const int i = i0 + 64 * (x >> 1) + 32 * wi + 16 * (x & 1) + 4 * lq;
-      const int j = j0 + 64 * (y >> 1) + 32 * wj + 16 * (y & 1) + li;
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (i < cols && j < cols && (i0 != j0 || i + v <= j) && !(fabsf(acc[x][y][v]) < INFINITY)) {
-          G[int64_t(j) * cols + i + v] = acc[x][y][v];
-          G[int64_t(i + v) * cols + j] = acc[x][y][v];
-        }
-    }
+  gram_classes<T, NS>(A, rows, cols, smem, G, i0, j0);
 }
 
 // F[i][j] = F[j][i] = ||G_ij||_F^2 (i <= j), one work-group a block, fixed-order
