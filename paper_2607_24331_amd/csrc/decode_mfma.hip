@@ -423,9 +423,10 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   // fixed splits: sequence and first page by number; balanced ones (SCHED) by
   // the unit's record where the cut is another than the fixed one.  The loads
   // below start with the fixed cut's numbers, beside those that tell which cut
-  // it is: 4 sequences of 32768 tokens on the 32/8-head layer take 87.9 us
-  // with fixed splits alone, 89.4 where every load waits for the record, 88.4
-  // so.
+  // it is: 4 sequences of 32768 tokens on the 32/8-head layer take 87.8 us
+  // with fixed splits alone, 89.2 where every load waits for the record, 88.0
+  // so (88.5 with the query blocks' loads after the lengths); 16 of 4096 to
+  // 8192 tokens 86.8 / 82.8 / 81.7.
   int b = u / n_split;
   const int split = u - b * n_split;
   int page0 = split * (split_tokens >> 6);
@@ -454,6 +455,9 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   // (every load is unconditional at a clamped, valid address, so no branch
   // hides a load from the wait counting; unused values are dropped)
   const int len_lane = SCHED ? seq_lens[min(int(threadIdx.x & 63), batch - 1)] : 0;
+  // the record by a lane load, before the query blocks' (a wait for it is none
+  // for them) and waited for only where it is used
+  const int rec = SCHED ? reinterpret_cast<const int*>(sched + u)[threadIdx.x & 3] : 0;
   constexpr int SWc = (4 * NT < W) ? 4 * NT : W;
   const int hrow_raw = mt.hord[slice][min(16 * ((min(w, SWc - 1) * ((4 * NT) / SWc)) / 4) + lr, kSliceHeads - 1)];
   const int hrow = w < SWc ? hrow_raw : -1;
@@ -470,7 +474,6 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
   bool fixed = true;
   int t1 = 0;
   if constexpr (SCHED) {
-    const int rec = reinterpret_cast<const int*>(sched + u)[lane & 3];   // a lane load: not waited for unless used
     bool fits = fixed_fits(len_lane, max_context, fixed_pages);
     for (int k = 64; k < batch; k += 64)
       fits &= fixed_fits(seq_lens[min(lane + k, batch - 1)], max_context, fixed_pages);
@@ -489,7 +492,8 @@ __global__ __launch_bounds__(W * 64, 1) void split_mfma(
       if (b != b_fixed) {
         qsrc = qblk_ws + int64_t(b * J + slice) * mt.max_pairs * 128;
 #pragma unroll
-        for (int k = 0; k < kQblkLoads; ++k) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
+        for (int k = 0; k < kQblkLoads; ++k)
+          if (k * W * 64 < n16) qv[k] = qsrc[min(tid + k * W * 64, n16 - 1)];
       }
       T_b = seq_lens[b];
     }
