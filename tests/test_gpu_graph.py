@@ -106,3 +106,45 @@ def test_rotary_graph_replays_equal_eager():
         torch.cuda.synchronize()
         assert torch.equal(out, eager), f"replay {r} differs"
         del scratch
+
+
+def test_graph_of_balanced_splits_follows_the_lengths():
+    # automatic splits cut on the device: replays of one capture with lengths
+    # alike (the fixed cut), unlike (records) and empty, in turn, over a
+    # workspace overwritten between replays
+    from paper_2607_24331_amd import Plan, decode
+    plan = Plan(512, 8, 4, 64, (0, 1, 1, 0), (60, 45), 144)
+    B, top = 3, 12000
+    pages = -(-top // 64)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    pool = rnd(B * pages, plan.page_elems).to(torch.bfloat16)
+    table = torch.randperm(B * pages, generator=g, device="cuda").to(torch.int32).view(B, pages)
+    q, lens = rnd(B, 8, 64), torch.full((B,), top, dtype=torch.int32, device="cuda")
+    Rk = (rnd(plan.key_factor_elems) / 8).to(torch.bfloat16)
+    Rv = (rnd(144, 256) / 16).to(torch.bfloat16)
+    out, ws = torch.empty_like(q), plan.new_workspace(B, top)
+
+    def step(o, w):
+        decode(plan, q, pool, table, lens, top, Rk, Rv, out=o, workspace=w)
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        step(out, ws)
+    torch.cuda.current_stream().wait_stream(s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(out, ws)
+    eager = torch.empty_like(out)
+    for now in ((top,) * B, (top, 100, 5000), (0, 0, 0), (11000, top, 10500), (1, top, 0), (top,) * B):
+        lens.copy_(torch.tensor(now, dtype=torch.int32))
+        step(eager, plan.new_workspace(B, top))
+        ws.fill_(0)                             # records left from the replay before are gone
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager), now
